@@ -24,7 +24,9 @@
 // issued between the current half's exponentials, then its PV MFMAs.  Built
 // without IEEE NaN quieting, so the row max is plain v_max3_f32.
 //
-// fp32 path (and unsupported shapes): one thread per query, online softmax.
+// Other head sizes and fp32 run in k_attention_general.hip; shapes that neither
+// takes (unaligned pointers or bands, ragged key counts): one thread per query,
+// online softmax.
 #include "common.h"
 #include "kernels.h"
 
@@ -694,7 +696,8 @@ __global__ __launch_bounds__(MergeGeo<D>::THREADS) void attn_merge_kernel(AttnPa
 }
 
 // ---------------------------------------------------------------------------
-// SIMT attention: one thread per (branch, head, query).
+// SIMT attention (shapes outside both matrix-core kernels): one thread per
+// (branch, head, query).
 template <typename T, int D>
 __global__ __launch_bounds__(64) void attn_simt_kernel(AttnParams p) {
   const int q = blockIdx.x * 64 + threadIdx.x;
@@ -855,6 +858,7 @@ hipError_t launch_attention(const AttnParams& p0, int dtype, hipStream_t s) {
     }
     return hipGetLastError();
   }
+  if (attention_general_ok(p, dtype)) return launch_attention_general(p, dtype, s);
   if (dtype == kBF16) return launch_simt<bf16>(p, s);
   return launch_simt<float>(p, s);
 }

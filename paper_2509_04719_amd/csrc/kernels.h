@@ -77,6 +77,9 @@ struct AttnParams {
   // 1: q already carries log2(e)/sqrt(d) (the step's QKV epilogue applies it
   // before rounding); 0: the kernels apply it
   int q_scaled = 0;
+  // 1: every query's sums in an order that its token alone fixes (no split of
+  // the keys that depends on the shape of the call)
+  int fixed_order = 0;
 };
 
 // Workspace bytes that let the attention cut query tiles between workgroups
@@ -84,6 +87,10 @@ struct AttnParams {
 size_t attention_workspace_bytes(int B, int heads, int n_q, int n_kv, int d, int dtype);
 hipError_t launch_attention(const AttnParams& p, int dtype, hipStream_t stream);
 bool attention_uses_mfma(int d, int n_kv, int dtype);
+// bf16 heads of 32, 80, 96 and 128 channels and every fp32 head size, where
+// alignment and key count allow (k_attention_general.hip).
+bool attention_general_ok(const AttnParams& p, int dtype);
+hipError_t launch_attention_general(const AttnParams& p, int dtype, hipStream_t stream);
 
 // Conditioning.  temb: fp32 [H] scratch; sc: fp32 [B][H] SiLU(c);
 // mod: fp32 [B][n_mod].

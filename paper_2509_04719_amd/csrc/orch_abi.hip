@@ -625,6 +625,7 @@ int run_step(orch_ctx* x, const float* x_full, int rb, int re, int t, int t_prev
     ap.B = B; ap.heads = x->heads; ap.n_q = n_tok; ap.n_kv = x->n_kv; ap.d = x->d; ap.out = x->att;
     ap.q_scaled = q_scaled;
     ap.ws = attn_ws; ap.ws_bytes = x->attn_ws_bytes;
+    ap.fixed_order = !x->work_split;
     {
       KernelTimer kt(x, ORCH_KCLASS_ATTENTION, s);
       HIP_TRY(launch_attention(ap, dt, s), "attention launch");
