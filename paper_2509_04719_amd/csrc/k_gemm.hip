@@ -3,8 +3,8 @@
 // the QKV scatter into the head-major Q buffer and the K / V^T buffer).
 //
 // bf16 path: MFMA tiles fed by direct-to-LDS loads (described at the kernel).
-// fp32 path (and shapes the MFMA tiling does not cover): a 64x64 SIMT tile
-// with 4x4 outputs per thread.
+// fp32 path: 32x32x2 fp32 MFMAs (described at the kernel).  Shapes and pointers
+// neither takes: a 64x64 SIMT tile with 4x4 outputs per thread.
 #include <cstdlib>
 #include <type_traits>
 
@@ -568,7 +568,116 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(const bf16* __r
 }
 
 // ---------------------------------------------------------------------------
-// SIMT GEMM (fp32, and fallback shapes)
+// fp32 GEMM on v_mfma_f32_32x32x2_f32 (fp32 products and sums; 154 TFLOP/s in a
+// large library product, twice the vector unit without packed instructions).
+// A workgroup is four waves: (BM / 32) x (BN / 32) blocks of 32 x 32 outputs x KG
+// groups that share the k-tiles (group g takes tiles g, g + KG, ...; their sums
+// meet in LDS, added in group order).  k-tiles of 32 (128-byte rows) go straight
+// into LDS, a ring of S stages per group, 16-byte chunks XOR-swizzled by row as
+// in the bf16 kernel.  A fragment read gives a lane four consecutive k of its
+// row, one for each of four MFMAs: MFMA e of chunk pair c adds k = 8 c + e and
+// 8 c + 4 + e, the same order in every configuration without key groups.
+template <int BM, int BN, int KG, int S>
+struct GemmF32Geo {
+  static constexpr int BK = 32, NWG = 4 / KG;             // waves per group
+  static constexpr int WN = BN / 32;
+  static constexpr int STAGE = (BM + BN) * BK * 4;
+  static constexpr int LPT = (BM + BN) / 8 / NWG;         // 1 KB loads per wave and k-tile
+  static constexpr int LDS = KG * S * STAGE;
+  static_assert((BM / 32) * (BN / 32) == NWG, "a 32 x 32 block per wave");
+  static_assert((BM + BN) / 8 % NWG == 0, "whole loads");
+  static_assert((KG - 1) * NWG * 4096 <= LDS, "the groups' sums fit the ring");
+};
+
+template <int BM, int BN, int KG, int S, int EPI>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ W,
+                                                       int M, int N, int K, int tiles_n, EpiParams ep) {
+  using G = GemmF32Geo<BM, BN, KG, S>;
+  constexpr int LPT = G::LPT;
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  const int lane = threadIdx.x & 63, lr = lane & 31, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wg = wave % G::NWG, kg = wave / G::NWG;
+  const int m0 = (int)blockIdx.x / tiles_n * BM, n0 = (int)blockIdx.x % tiles_n * BN;
+  char* ring = smem + kg * S * G::STAGE;
+
+  // load j of a stage: rows 8 j .. + 8 (A first, then W); rows past the matrix
+  // re-read its last one
+  const char* src[LPT];
+#pragma unroll
+  for (int i = 0; i < LPT; ++i) {
+    const int r = (wg * LPT + i) * 8 + (lane >> 3);
+    const int ch = (lane & 7) ^ ((r >> 1) & 7);
+    const float* row = r < BM ? A + (size_t)min(m0 + r, M - 1) * K : W + (size_t)min(n0 + r - BM, N - 1) * K;
+    src[i] = reinterpret_cast<const char*>(row + ch * 4);
+  }
+  // this group's t-th k-tile into stage st
+  auto issue = [&](int t, int st) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < LPT; ++i)
+      __builtin_amdgcn_global_load_lds((const ORCH_GLB void*)(src[i] + (size_t)(kg + KG * t) * (G::BK * 4)),
+                                       (ORCH_LDS void*)(ring + st * G::STAGE + (wg * LPT + i) * 1024), 16, 0, 0);
+  };
+  const int arow = (wg / G::WN * 32 + lr) * 128, brow = (BM + wg % G::WN * 32 + lr) * 128;
+  int koff[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) koff[c] = ((2 * c + h) ^ ((lr >> 1) & 7)) * 16;
+  f32x16 acc;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+
+  // groups differ by at most one k-tile; all meet every barrier
+  const int KT = K / G::BK, mine = (KT - kg + KG - 1) / KG, NIT = (KT + KG - 1) / KG;
+#pragma unroll
+  for (int t = 0; t < S - 1; ++t)
+    if (t < mine) issue(t, t);
+  for (int t = 0; t < NIT; ++t) {
+    if (t + S - 2 < mine) wait_vmcnt<(S - 2) * LPT>();
+    else wait_vmcnt<0>();
+    lds_barrier();
+    if (t + S - 1 < mine) issue(t + S - 1, (t + S - 1) % S);
+    if (t >= mine) continue;
+    const char* base = ring + t % S * G::STAGE;
+    f32x4 a[4], b[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      a[c] = *reinterpret_cast<const f32x4*>(base + arow + koff[c]);
+      b[c] = *reinterpret_cast<const f32x4*>(base + brow + koff[c]);
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[c][e], b[c][e], acc, 0, 0, 0);
+  }
+  if constexpr (KG > 1) {
+    lds_barrier();
+    if (kg > 0) {
+      float* part = reinterpret_cast<float*>(smem + ((kg - 1) * G::NWG + wg) * 4096) + lane;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) part[r * 64] = acc[r];
+    }
+    __syncthreads();
+    if (kg > 0) return;
+#pragma unroll
+    for (int g = 0; g < KG - 1; ++g) {
+      const float* part = reinterpret_cast<const float*>(smem + (g * G::NWG + wg) * 4096) + lane;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[r] += part[r * 64];
+    }
+  }
+  // a lane holds column lr, rows 8 g + 4 h .. + 4
+  const Epilogue<float, EPI> epi{ep, M, N};
+  const int n = n0 + wg % G::WN * 32 + lr;
+  const auto col = epi.column(n);
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    const float v[4] = {acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]};
+    epi.store4(col, m0 + wg / G::WN * 32 + 8 * g + 4 * h, n, v);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// SIMT GEMM (shapes and pointers the matrix-core kernels do not take)
 namespace simt_gemm {
 constexpr int BM = 64, BN = 64, BK = 16;
 }
@@ -756,6 +865,34 @@ static void launch_tile_cfg(int c, const void* A, const void* W, int M, int N, i
   }
 }
 
+template <int BM, int BN, int KG, int S, int EPI>
+static void launch_f32_tile(const void* A, const void* W, int M, int N, int K, const EpiParams& ep, hipStream_t s) {
+  using G = GemmF32Geo<BM, BN, KG, S>;
+  auto kern = gemm_f32_kernel<BM, BN, KG, S, EPI>;
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, G::LDS);
+  (void)attr;
+  const int tn = ceil_div(N, BN);
+  hipLaunchKernelGGL(kern, dim3(ceil_div(M, BM) * tn), dim3(256), G::LDS, s, reinterpret_cast<const float*>(A),
+                     reinterpret_cast<const float*>(W), M, N, K, tn, ep);
+}
+
+// The split of the four waves.  A 32 x 32 block is one wave's chain of K / 2 MFMAs
+// (64 cycles each), so with few blocks the key groups shorten it, and with some
+// thousands the two-group tile still spreads them more evenly; with more, the 64 x
+// 64 tile loads half the bytes per product.  Measured us for (64, 64, 1) / (32, 64, 2)
+// / (32, 32, 4): 96 x 1536 -> 384 (36 blocks) 40 / 26 / 16; 1000 x 1536 -> 384
+// (384) 43 / 29 / 27; 1000 x 384 -> 1152 (1152) 19.4 / 17.4 / 20.7; 2000 x 3072 -> 768
+// (1512) 125 / 100 / 121; 4096 x 4608 -> 1152 (4608) 446 / 418 / 496; 4096 x 1152 ->
+// 4608 (18432) 398 / 430 / 584.  (The 64 x 64 SIMT tile: 1000 x 384 -> 1152 54 us.)
+template <int EPI>
+static void launch_f32(const void* A, const void* W, int M, int N, int K, const EpiParams& ep, hipStream_t s) {
+  const long long blocks = (long long)ceil_div(M, 32) * ceil_div(N, 32);
+  if (ep.fixed_order || blocks > 8192) launch_f32_tile<64, 64, 1, 3, EPI>(A, W, M, N, K, ep, s);
+  else if (blocks > 512) launch_f32_tile<32, 64, 2, 2, EPI>(A, W, M, N, K, ep, s);
+  else launch_f32_tile<32, 32, 4, 2, EPI>(A, W, M, N, K, ep, s);
+}
+
 template <int EPI>
 static hipError_t launch_gemm_epi(const void* A, const void* W, int M, int N, int K,
                                   const EpiParams& ep, int dtype, hipStream_t s) {
@@ -770,6 +907,8 @@ static hipError_t launch_gemm_epi(const void* A, const void* W, int M, int N, in
     } else {
       launch_tile_cfg<EPI>(c, A, W, M, N, K, ep, s, 1);
     }
+  } else if (dtype == kF32 && K % 32 == 0 && aligned16(A) && aligned16(W)) {
+    launch_f32<EPI>(A, W, M, N, K, ep, s);
   } else {
     dim3 grid(ceil_div(N, simt_gemm::BN), ceil_div(M, simt_gemm::BM));
     if (dtype == kBF16)

@@ -32,6 +32,8 @@ struct EpiParams {
   // the machine split K (partials [splits][M][N], then a reduction)
   float* ws = nullptr;
   size_t ws_elems = 0;
+  // true: every output's sum in an order that does not depend on M
+  bool fixed_order = false;
 };
 
 // Workspace elements (fp32) the GEMM's k-split takes for this shape (0: no split).

@@ -596,7 +596,7 @@ int run_step(orch_ctx* x, const float* x_full, int rb, int re, int t, int t_prev
     EpiParams eq{};
     eq.q_scale = q_scaled ? 1.4426950408889634f / sqrtf((float)x->d) : 1.0f;
     eq.bias = x->b_qkv[l];
-    eq.ws = gemm_ws; eq.ws_elems = x->gemm_ws_elems;
+    eq.ws = gemm_ws; eq.ws_elems = x->gemm_ws_elems; eq.fixed_order = !x->work_split;
     eq.rows_per_batch = n_tok;
     eq.q = x->q;
     eq.heads = x->heads; eq.hidden = H; eq.head_dim = x->d;
@@ -634,7 +634,7 @@ int run_step(orch_ctx* x, const float* x_full, int rb, int re, int t, int t_prev
     EpiParams eo{};
     eo.out = x->h; eo.bias = x->b_proj[l]; eo.gate = mb + 2 * H; eo.gate_stride = x->n_mod;
     eo.rows_per_batch = n_tok;
-    eo.ws = gemm_ws; eo.ws_elems = x->gemm_ws_elems;
+    eo.ws = gemm_ws; eo.ws_elems = x->gemm_ws_elems; eo.fixed_order = !x->work_split;
     {
       KernelTimer kt(x, ORCH_KCLASS_PROJ, s);
       HIP_TRY(launch_gemm(x->att, x->w_proj[l], M, H, H, kEpiResidual, eo, dt, s), "proj launch");
@@ -647,7 +647,7 @@ int run_step(orch_ctx* x, const float* x_full, int rb, int re, int t, int t_prev
 
     EpiParams e1{};
     e1.out = x->mlp; e1.bias = x->b_fc1[l];
-    e1.ws = gemm_ws; e1.ws_elems = x->gemm_ws_elems;
+    e1.ws = gemm_ws; e1.ws_elems = x->gemm_ws_elems; e1.fixed_order = !x->work_split;
     {
       KernelTimer kt(x, ORCH_KCLASS_FC1, s);
       HIP_TRY(launch_gemm(x->u, x->w_fc1[l], M, F, H, kEpiGelu, e1, dt, s), "fc1 launch");
@@ -656,7 +656,7 @@ int run_step(orch_ctx* x, const float* x_full, int rb, int re, int t, int t_prev
     EpiParams e2{};
     e2.out = x->h; e2.bias = x->b_fc2[l]; e2.gate = mb + 5 * H; e2.gate_stride = x->n_mod;
     e2.rows_per_batch = n_tok;
-    e2.ws = gemm_ws; e2.ws_elems = x->gemm_ws_elems;
+    e2.ws = gemm_ws; e2.ws_elems = x->gemm_ws_elems; e2.fixed_order = !x->work_split;
     {
       KernelTimer kt(x, ORCH_KCLASS_FC2, s);
       HIP_TRY(launch_gemm(x->mlp, x->w_fc2[l], M, H, F, kEpiResidual, e2, dt, s), "fc2 launch");
