@@ -2,7 +2,7 @@
 // (plain store, GELU, gated residual add into the fp32 residual stream, and
 // the QKV scatter into the head-major Q buffer and the K / V^T buffer).
 //
-// bf16 path: MFMA tiles fed by direct-to-LDS loads (described at the kernel).
+// bf16 path: MFMA tiles fed by direct-to-LDS loads (described at the kernels).
 // fp32 path: 32x32x2 fp32 MFMAs (described at the kernel).  Shapes and pointers
 // neither takes: a 64x64 SIMT tile with 4x4 outputs per thread.
 #include <cstdlib>
@@ -178,19 +178,20 @@ struct StripEpilogue {
     f32x4 h[PRE_H ? RIT : 1], g[PRE_H ? RIT : 1], rb[PRE_H ? RIT : 1];
   };
 
-  __device__ __forceinline__ void prefetch(Pre& pre, int lane, int m0, int n0) const {
+  // bias: that of column n0 (global memory or LDS)
+  __device__ __forceinline__ void prefetch(Pre& pre, int lane, int m0, int n0, const float* bias) const {
     if constexpr (BIAS8) {
       constexpr int CH = TN / 8;
 #pragma unroll
       for (int q = 0; q < NB; ++q) {
-        const int n = n0 + ((q * 64 + lane) % CH) * 8;
-        pre.b[q][0] = *reinterpret_cast<const f32x4*>(ep.bias + n);
-        pre.b[q][1] = *reinterpret_cast<const f32x4*>(ep.bias + n + 4);
+        const int n = ((q * 64 + lane) % CH) * 8;
+        pre.b[q][0] = *reinterpret_cast<const f32x4*>(bias + n);
+        pre.b[q][1] = *reinterpret_cast<const f32x4*>(bias + n + 4);
       }
     }
     if constexpr (EPI == kEpiQkv) {
 #pragma unroll
-      for (int q = 0; q < TN / 16; ++q) pre.vb[q] = ep.bias[n0 + q * 16 + (lane >> 2)];
+      for (int q = 0; q < TN / 16; ++q) pre.vb[q] = bias[q * 16 + (lane >> 2)];
     }
     if constexpr (PRE_H) {
       constexpr int CH = TN / 4;
@@ -420,6 +421,26 @@ struct GemmGeo {
   static_assert(S * STAGE <= 160 * 1024, "LDS");
 };
 
+// Which tile a workgroup takes: workgroup b is in split b / T of T = tiles_m x
+// tiles_n tiles; inside a split XCD-major, then groups of 8 tile rows,
+// column-major inside.
+struct TileAt {
+  int split, m, n;
+  __device__ __forceinline__ TileAt(int tiles_m, int tiles_n) {
+    const int T = tiles_m * tiles_n;
+    split = __builtin_amdgcn_readfirstlane(blockIdx.x / T);
+    int pid = blockIdx.x - split * T;
+    const int per = T / 8;
+    if (pid < per * 8) pid = (pid & 7) * per + (pid >> 3);
+    constexpr int GROUP = 8;
+    const int gid = pid / (GROUP * tiles_n);
+    const int first_m = gid * GROUP;
+    const int gsz = min(tiles_m - first_m, GROUP);
+    m = first_m + (pid % (GROUP * tiles_n)) % gsz;
+    n = (pid % (GROUP * tiles_n)) / gsz;
+  }
+};
+
 template <int BM, int BN, int BK, int WM, int WN, int S, int EPI>
 __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(const bf16* __restrict__ A,
                                                         const bf16* __restrict__ W, int M, int N,
@@ -436,21 +457,10 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(const bf16* __r
   const int wm = wave / WN, wn = wave % WN;
 
   // K is this workgroup's k extent, ldk the row stride of A and W: with a
-  // k-split, workgroup b takes split b / T, keys [split K, (split + 1) K).
-  // Tile order inside a split: XCD-major, then groups of 8 tile rows,
-  // column-major inside.
-  const int T = tiles_m * tiles_n;
-  const int split = __builtin_amdgcn_readfirstlane(blockIdx.x / T);
-  int pid = blockIdx.x - split * T;
-  const int per = T / 8;
-  if (pid < per * 8) pid = (pid & 7) * per + (pid >> 3);
-  constexpr int GROUP = 8;
-  const int gid = pid / (GROUP * tiles_n);
-  const int first_m = gid * GROUP;
-  const int gsz = min(tiles_m - first_m, GROUP);
-  const int tile_m = first_m + (pid % (GROUP * tiles_n)) % gsz;
-  const int tile_n = (pid % (GROUP * tiles_n)) / gsz;
-  const int m0 = tile_m * BM, n0 = tile_n * BN;
+  // k-split, split s takes keys [s K, (s + 1) K)
+  const TileAt at(tiles_m, tiles_n);
+  const int split = at.split;
+  const int m0 = at.m * BM, n0 = at.n * BN;
 
   // byte offset of this lane's source chunk in each wave-level load: load j
   // covers tile rows (j * NW + wave) * RPL .. + RPL - 1 (A rows first, then
@@ -541,7 +551,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(const bf16* __r
   using E = StripEpilogue<FM, FN, EPI>;
   const E epi{ep, M, N, split};
   typename E::Pre pre;
-  epi.prefetch(pre, lane, m0 + wm * G::TM, n0 + wn * G::TN);
+  epi.prefetch(pre, lane, m0 + wm * G::TM, n0 + wn * G::TN, ep.bias + n0 + wn * G::TN);
 
 #pragma unroll
   for (int s = 0; s < S - 1; ++s) static_for<0, LPT>([&](auto jc) { dma(jc, s, s); });
@@ -565,6 +575,183 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(const bf16* __r
   lds_barrier();
   epi.run(acc, reinterpret_cast<float*>(smem + wave * E::BYTES), lane, m0 + wm * G::TM, n0 + wn * G::TN,
           pre);
+}
+
+// ---------------------------------------------------------------------------
+// The 256 x 256 tile in phases: eight waves (2 x 4, 128 x 64 outputs each), k-tiles
+// of 64 in two LDS stages.  A k-tile takes four phases, one for each quarter
+// (i, j) of the wave's tile: 64 rows (half i of A) x 32 columns (half j of W),
+// eight MFMAs, in the order (0,0) (0,1) (1,1) (1,0).  Between its MFMAs a phase
+// reads the fragments of the next one (each half has registers of its own, W's
+// two halves swapping sets every k-tile) and loads one half-tile two k-tiles
+// ahead into the stage just read:
+//
+//   phase  MFMAs  reads        loads
+//   P0     A0 W0  W1(kt)       A0(kt + 2)
+//   P1     A0 W1  A1(kt)       W0(kt + 2)
+//   P2     A1 W1  A0(kt + 1)   W1(kt + 2)
+//   P3     A1 W0  W0(kt + 1)   A1(kt + 2)
+//
+// A barrier before P0 and one before P2: each publishes the two halves read
+// until the next (loaded six or more phases earlier: vmcnt(8) leaves the four
+// younger half-tiles in flight) and frees the two read since the last.  So no
+// MFMA waits for an LDS round trip behind a barrier, and a load has 1.5 k-tiles to
+// land; gemm_bf16_kernel reads a k-tile's first fragments after its barrier and
+// loads one k-tile ahead.
+// k runs in the same order as there, 16 at a time: the same bits.
+namespace ph {
+constexpr int BM = 256, BN = 256, BK = 64, KK = 4, HALF = 128 * BK * 2, LDS = 8 * HALF + BN * 4;
+enum { kA0 = 0, kA1 = 1, kW0 = 2, kW1 = 3 };
+// half x of stage st: A's four in the first 64 KB, W's in the second (read
+// offsets within 16 bits of one base each)
+constexpr int at(int x, int st) { return ((x & 2) * 2 + st * 2 + (x & 1)) * HALF; }
+}  // namespace ph
+
+template <int EPI>
+__global__ __launch_bounds__(512) void gemm_bf16_phased_kernel(const bf16* __restrict__ A, const bf16* __restrict__ W,
+                                                               int M, int N, int K, int ldk, int tiles_m, int tiles_n,
+                                                               EpiParams ep) {
+  // (device-only types: the host pass needs the launch stub alone)
+#if defined(__HIP_DEVICE_COMPILE__)
+  using namespace ph;
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  const int lane = threadIdx.x & 63, lr = lane & 31, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave >> 2, wn = wave & 3;
+  const TileAt ta(tiles_m, tiles_n);
+  const int m0 = ta.m * BM, n0 = ta.n * BN;
+
+  // Half X's row r is row 128 (r / 64) + 64 i + r % 64 of A's tile, 64 (r / 32) +
+  // 32 j + r % 32 of W's: each wave's 128 x 64 outputs are contiguous.  Load l of
+  // a half fills rows 8 l .. + 8, this wave's are l = 2 wave, 2 wave + 1; chunk c
+  // of row r lies at c ^ (r / 2 % 8).  A rows past M re-read row M - 1.
+  unsigned off[4][2];
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int r = (2 * wave + q) * 8 + (lane >> 3);
+    const unsigned ch = (unsigned)((lane & 7) ^ ((r >> 1) & 7)) * 16u;
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+      off[kA0 + x][q] = (unsigned)min(m0 + 128 * (r >> 6) + 64 * x + (r & 63), M - 1) * (unsigned)ldk * 2u + ch;
+      off[kW0 + x][q] = (unsigned)(n0 + 64 * (r >> 5) + 32 * x + (r & 31)) * (unsigned)ldk * 2u + ch;
+    }
+  }
+  // (buffer loads: the k-tile is a scalar offset, the lane's offset constant; the
+  // launcher keeps both matrices under 2 GiB)
+  const __amdgpu_buffer_rsrc_t rA = buffer_rsrc(A + (size_t)ta.split * K, ((size_t)(M - 1) * ldk + K) * 2);
+  const __amdgpu_buffer_rsrc_t rW = buffer_rsrc(W + (size_t)ta.split * K, ((size_t)(N - 1) * ldk + K) * 2);
+  // load q of half x of k-tile kt into stage st
+  auto load = [&](int x, int q, int st, int kt) __attribute__((always_inline)) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(x < kW0 ? rA : rW,
+                                             (ORCH_LDS void*)(smem + at(x, st) + (2 * wave + q) * 1024), 16, off[x][q],
+                                             (unsigned)kt * (BK * 2), 0, 0);
+  };
+
+  f32x16 acc[4][2];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+
+  // (two LDS bases per k-step, the rest in the read's 16-bit offset; the empty asm
+  // keeps the compiler from moving the 64 KB out of W's)
+  int a_rd[KK], w_rd[KK];
+#pragma unroll
+  for (int kk = 0; kk < KK; ++kk) {
+    const int ko = ((2 * kk + h) ^ ((lr >> 1) & 7)) * 16;
+    a_rd[kk] = (64 * wm + lr) * BK * 2 + ko;
+    w_rd[kk] = at(kW0, 0) + (32 * wn + lr) * BK * 2 + ko;
+    asm volatile("" : "+v"(w_rd[kk]));
+  }
+  bf16x8 fa[2][2 * KK], fw[2][KK];   // A halves (two 32-row blocks), W halves
+  // fragment e of a half: k-step e / 2, block e % 2 of A; k-step e of W
+  auto read_a = [&](int x, int st, int e) __attribute__((always_inline)) {
+    fa[x][e] = *reinterpret_cast<const bf16x8*>(smem + a_rd[e >> 1] + at(kA0 + x, st) + (e & 1) * 32 * BK * 2);
+  };
+  auto read_w = [&](int x, int st, int set, int e) __attribute__((always_inline)) {
+    fw[set][e] = *reinterpret_cast<const bf16x8*>(smem + w_rd[e] + (at(kW0 + x, st) - at(kW0, 0)));
+  };
+  // at most `ahead` loads in flight, every fragment read arrived, then the barrier
+  auto sync = [&](auto ahead_c) __attribute__((always_inline)) {
+    wait_vmcnt<decltype(ahead_c)::value>();
+    __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
+    __builtin_amdgcn_sched_barrier(0);
+    lds_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // quarter (i, j) from W's register set; f(e) follows MFMA e
+  auto quarter = [&](auto ic, auto jc, auto set_c, auto&& f) __attribute__((always_inline)) {
+    constexpr int i = decltype(ic)::value, j = decltype(jc)::value, set = decltype(set_c)::value;
+    static_for<0, 2 * KK>([&](auto ec) {
+      constexpr int e = decltype(ec)::value, b = e & 1;
+      acc[2 * i + b][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw[set][e >> 1], fa[i][e], acc[2 * i + b][j], 0, 0, 0);
+      f(e);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  };
+  using E = StripEpilogue<4, 2, EPI>;
+  const E epi{ep, M, N, ta.split};
+  typename E::Pre pre;
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
+  // k-tile kt in stage ST (its W0 in set ST).  LEFT: k-tiles after it, 2: two or
+  // more, so the loads go on
+  auto ktile = [&](auto st_c, auto left_c, int kt) __attribute__((always_inline)) {
+    constexpr int ST = decltype(st_c)::value, LEFT = decltype(left_c)::value;
+    constexpr bool L = LEFT == 2;
+    using S0 = std::integral_constant<int, ST>;
+    using S1 = std::integral_constant<int, ST ^ 1>;
+    sync(std::integral_constant<int, LEFT == 0 ? 0 : 8>{});
+    quarter(I0{}, I0{}, S0{}, [&](int e) __attribute__((always_inline)) {
+      if (e < KK) read_w(1, ST, ST ^ 1, e);
+      if (L && (e & 3) == 3) load(kA0, e >> 2, ST, kt + 2);
+    });
+    quarter(I0{}, I1{}, S1{}, [&](int e) __attribute__((always_inline)) {
+      read_a(1, ST, e);
+      if (L && (e & 3) == 3) load(kW0, e >> 2, ST, kt + 2);
+    });
+    if constexpr (LEFT > 0) sync(std::integral_constant<int, L ? 8 : 4>{});
+    quarter(I1{}, I1{}, S1{}, [&](int e) __attribute__((always_inline)) {
+      if (LEFT > 0) read_a(0, ST ^ 1, e);
+      if (L && (e & 3) == 3) load(kW1, e >> 2, ST, kt + 2);
+    });
+    quarter(I1{}, I0{}, S0{}, [&](int e) __attribute__((always_inline)) {
+      if (LEFT > 0 && e < KK) read_w(0, ST ^ 1, ST ^ 1, e);
+      if (L && (e & 3) == 3) load(kA1, e >> 2, ST, kt + 2);
+    });
+  };
+
+  const int KT = K / BK;   // even (checked by the launcher)
+  // the tile's bias first, past the stages (it is cold in a step, and there is no
+  // register for it to wait in)
+  if (wave == 0)
+    __builtin_amdgcn_global_load_lds((const ORCH_GLB void*)(ep.bias + n0 + 4 * lane), (ORCH_LDS void*)(smem + 8 * HALF),
+                                     16, 0, 0);
+#pragma unroll
+  for (int kt = 0; kt < 2; ++kt)
+    for (const int x : {kA0, kW0, kW1, kA1})
+      for (int q = 0; q < 2; ++q) load(x, q, kt, kt);
+  wait_vmcnt<12>();
+  lds_barrier();
+#pragma unroll
+  for (int e = 0; e < 2 * KK; ++e) read_a(0, 0, e);
+#pragma unroll
+  for (int e = 0; e < KK; ++e) read_w(0, 0, 0, e);
+  int kt = 0;
+  for (; kt + 2 < KT; kt += 2) {
+    ktile(I0{}, std::integral_constant<int, 2>{}, kt);
+    ktile(I1{}, std::integral_constant<int, 2>{}, kt + 1);
+  }
+  ktile(I0{}, I1{}, kt);
+  ktile(I1{}, I0{}, kt + 1);
+
+  static_assert(8 * E::BYTES <= 8 * HALF, "epilogue staging fits the stages");
+  lds_barrier();
+  epi.prefetch(pre, lane, m0 + wm * 128, n0 + wn * 64, reinterpret_cast<const float*>(smem + 8 * HALF) + wn * 64);
+  epi.run(acc, reinterpret_cast<float*>(smem + wave * E::BYTES), lane, m0 + wm * 128, n0 + wn * 64, pre);
+#endif
 }
 
 // ---------------------------------------------------------------------------
@@ -739,7 +926,7 @@ struct TileCfg {
   float eff;  // measured relative throughput of the shape on a full machine
 };
 static const TileCfg kTiles[] = {
-    {256, 256, 64, 8, 2, 0.80f},
+    {256, 256, 64, 8, 2, 1.17f},
     {256, 192, 64, 8, 2, 1.00f},
     {128, 128, 64, 8, 4, 0.75f},
     {128, 64, 64, 4, 2, 0.30f},  // fallback: any N % 64 == 0, K % 64 == 0
@@ -759,10 +946,12 @@ static bool tile_fits(const TileCfg& t, int N, int K) {
 // Pick the configuration with the least estimated time: whole rounds of tiles
 // over the 256 CUs times the tile area, divided by the tile's relative
 // throughput per CU.  The throughputs were measured on the DiT-XL projection
-// shapes (K = 1152 and 4608, M from 768 to 8192): the 256x192 tile is the
-// fastest per CU, the 256x256 one wins when it fills the machine in one round
-// where 256x192 needs two, and the 128x128 one when 256-row tiles would leave
-// most CUs idle.
+// shapes (K = 1152 and 4608, M from 768 to 20480).  A round costs about 8 us
+// (first loads, epilogue) plus 1.55 us per 64-deep k-tile with 256x256 tiles,
+// 1.33 us with 256x192, and 6 us plus 0.49 us with 128x128: 1152 -> 4608 takes
+// 210 us in 6 rounds of 256x256 and 284 us in 8 rounds of 256x192 at M = 20480,
+// 131 (4) and 145 us (5) at 12288, 96.6 and 95.0 us (3 each) at 8192; the 128x128
+// tile wins when 256-row tiles would leave most CUs idle.
 static int pick_tile(int M, int N, int K) {
   const int f = forced_tile();
   if (f >= 0 && f < kNumTiles && tile_fits(kTiles[f], N, K)) return f;
@@ -855,10 +1044,34 @@ static int split_plan(int M, int N, int K, const TileCfg& t, size_t ws_elems) {
 }
 
 template <int EPI>
+static void launch_phased(const void* A, const void* W, int M, int N, int K, const EpiParams& ep0, hipStream_t s,
+                          int splits) {
+  EpiParams ep = ep0;
+  if (EPI == kEpiQkv) ep.hd_magic = (unsigned)((0x100000000ull + ep.head_dim - 1) / ep.head_dim);
+  auto kern = gemm_bf16_phased_kernel<EPI>;
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, ph::LDS);
+  (void)attr;
+  const int tm = ceil_div(M, ph::BM), tn = N / ph::BN;
+  hipLaunchKernelGGL(kern, dim3(tm * tn * splits), dim3(512), ph::LDS, s, reinterpret_cast<const bf16*>(A),
+                     reinterpret_cast<const bf16*>(W), M, N, K / splits, K, tm, tn, ep);
+}
+
+template <int EPI>
 static void launch_tile_cfg(int c, const void* A, const void* W, int M, int N, int K,
                             const EpiParams& ep, hipStream_t s, int splits) {
   switch (c) {
-    case 0: launch_tile<256, 256, 64, 2, 4, 2, EPI>(A, W, M, N, K, ep, s, splits); break;
+    case 0:
+      // More than one round: the phased kernel (1152 -> 4608, M = 20480: 229 -> 210
+      // us).  In a single round the plain loop: there the phased kernel is 2 us
+      // faster by itself (M = 3328 in a step: 38.4 -> 36.5 us), but the
+      // attention after it loses as much (71.9 -> 73.5 us) and the step 1%.
+      if (K / splits % 128 == 0 && ceil_div(M, ph::BM) * (N / ph::BN) * splits > 256 &&
+          (size_t)cmax(M, N) * K < (size_t)1 << 30)
+        launch_phased<EPI>(A, W, M, N, K, ep, s, splits);
+      else
+        launch_tile<256, 256, 64, 2, 4, 2, EPI>(A, W, M, N, K, ep, s, splits);
+      break;
     case 1: launch_tile<256, 192, 64, 4, 2, 2, EPI>(A, W, M, N, K, ep, s, splits); break;
     case 2: launch_tile<128, 128, 64, 4, 2, 4, EPI>(A, W, M, N, K, ep, s, splits); break;
     default: launch_tile<128, 64, 64, 2, 2, 2, EPI>(A, W, M, N, K, ep, s, splits); break;
