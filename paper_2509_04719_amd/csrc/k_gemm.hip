@@ -755,6 +755,125 @@ __global__ __launch_bounds__(512) void gemm_bf16_phased_kernel(const bf16* __res
 }
 
 // ---------------------------------------------------------------------------
+// bf16 GEMM for few output tiles: four waves, (BM / 32) x (BN / 32) blocks of
+// 32 x 32 outputs x KG groups that share the k (group g takes the stages g, g + KG,
+// ...; their sums meet in LDS, added in group order).  A stage is U k-tiles of 64,
+// laid out and swizzled as in gemm_bf16_kernel; a ring of S per group.  k runs in
+// the same order as there with one group: the same bits.
+template <int BM, int BN, int KG, int U, int S>
+struct GemmSmallGeo {
+  static constexpr int NWG = 4 / KG, WN = BN / 32;
+  static constexpr int TILE = (BM + BN) * 128;            // bytes of a k-tile
+  static constexpr int STAGE = U * TILE;
+  static constexpr int LPT = (BM + BN) / 8 / NWG;         // 1 KB loads per wave and k-tile
+  static constexpr int LDS = KG * S * STAGE;
+  static_assert((BM / 32) * (BN / 32) == NWG, "a 32 x 32 block per wave");
+  static_assert((BM + BN) / 8 % NWG == 0 && (S - 1) * U * LPT < 64, "whole loads");
+  static_assert((KG - 1) * NWG * 4096 <= LDS && LDS <= 160 * 1024, "LDS");
+};
+
+template <int BM, int BN, int KG, int U, int S, int EPI>
+__global__ __launch_bounds__(256) void gemm_bf16_small_kernel(const bf16* __restrict__ A, const bf16* __restrict__ W,
+                                                              int M, int N, int K, int tiles_n, EpiParams ep) {
+  using G = GemmSmallGeo<BM, BN, KG, U, S>;
+  constexpr int LPT = G::LPT;
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  const int lane = threadIdx.x & 63, lr = lane & 31, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wg = wave % G::NWG, kg = wave / G::NWG;
+  // row-major tiles, an eighth of them in a row on each XCD
+  int w = blockIdx.x;
+  const int per = gridDim.x / 8;
+  if (w < per * 8) w = (w & 7) * per + (w >> 3);
+  const int m0 = w / tiles_n * BM, n0 = w % tiles_n * BN;
+  const int mw = m0 + wg / G::WN * 32, nw = n0 + wg % G::WN * 32;
+  char* ring = smem + kg * S * G::STAGE;
+
+  using E = StripEpilogue<1, 1, EPI>;
+  const E epi{ep, M, N, 0};
+  typename E::Pre pre;
+  if (kg == 0) epi.prefetch(pre, lane, mw, nw, ep.bias + nw);
+
+  // load i of a k-tile: rows 8 (wg LPT + i) .. + 8 (A first, then W); A rows past
+  // M re-read row M - 1
+  unsigned off[LPT];
+  bool isa[LPT];
+#pragma unroll
+  for (int i = 0; i < LPT; ++i) {
+    const int r0 = (wg * LPT + i) * 8, r = r0 + (lane >> 3);
+    isa[i] = r0 < BM;
+    off[i] = ((isa[i] ? (unsigned)min(m0 + r, M - 1) : (unsigned)(n0 + r - BM)) * (unsigned)K +
+              ((lane & 7) ^ ((r >> 1) & 7)) * 8) * 2u;
+  }
+  const char* gA = reinterpret_cast<const char*>(A);
+  const char* gW = reinterpret_cast<const char*>(W);
+  // this group's t-th stage
+  auto issue = [&](int t) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int i = 0; i < LPT; ++i)
+        __builtin_amdgcn_global_load_lds(
+            (const ORCH_GLB void*)((isa[i] ? gA : gW) + (unsigned)((kg + KG * t) * U + u) * 128 + off[i]),
+            (ORCH_LDS void*)(ring + t % S * G::STAGE + u * G::TILE + (wg * LPT + i) * 1024), 16, 0, 0);
+  };
+  const int arow = (wg / G::WN * 32 + lr) * 128, wrow = (BM + wg % G::WN * 32 + lr) * 128;
+  int koff[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) koff[c] = ((2 * c + h) ^ ((lr >> 1) & 7)) * 16;
+  f32x16 acc[1][1];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[0][0][r] = 0.0f;
+
+  // groups differ by at most one stage; all meet every barrier
+  const int ST = K / (64 * U), mine = (ST - kg + KG - 1) / KG, NIT = (ST + KG - 1) / KG;
+#pragma unroll
+  for (int t = 0; t < S - 1; ++t)
+    if (t < mine) issue(t);
+  for (int t = 0; t < NIT; ++t) {
+    if (t + S - 2 < mine) wait_vmcnt<(S - 2) * U * LPT>();
+    else wait_vmcnt<0>();
+    lds_barrier();
+    if (t + S - 1 < mine) issue(t + S - 1);
+    if (t >= mine) continue;
+    const char* base = ring + t % S * G::STAGE;
+    bf16x8 a[U][4], b[U][4];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        a[u][c] = *reinterpret_cast<const bf16x8*>(base + u * G::TILE + arow + koff[c]);
+        b[u][c] = *reinterpret_cast<const bf16x8*>(base + u * G::TILE + wrow + koff[c]);
+      }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[u][c], a[u][c], acc[0][0], 0, 0, 0);
+  }
+  lds_barrier();
+  if constexpr (KG > 1) {
+    if (kg > 0) {
+      float* part = reinterpret_cast<float*>(smem + ((kg - 1) * G::NWG + wg) * 4096) + lane;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) part[r * 64] = acc[0][0][r];
+    }
+    __syncthreads();
+    if (kg > 0) return;
+#pragma unroll
+    for (int g = 0; g < KG - 1; ++g) {
+      const float* part = reinterpret_cast<const float*>(smem + (g * G::NWG + wg) * 4096) + lane;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[0][0][r] += part[r * 64];
+    }
+  }
+  // (the strips lie past the groups' sums)
+  constexpr int SUMS = (KG - 1) * G::NWG * 4096;
+  static_assert(SUMS + G::NWG * E::BYTES <= G::LDS, "strips fit the ring");
+  epi.run(acc, reinterpret_cast<float*>(smem + SUMS + wg * E::BYTES), lane, mw, nw, pre);
+}
+
+// ---------------------------------------------------------------------------
 // fp32 GEMM on v_mfma_f32_32x32x2_f32 (fp32 products and sums; 154 TFLOP/s in a
 // large library product, twice the vector unit without packed instructions).
 // A workgroup is four waves: (BM / 32) x (BN / 32) blocks of 32 x 32 outputs x KG
@@ -920,7 +1039,8 @@ __global__ __launch_bounds__(256) void gemm_simt_kernel(const T* __restrict__ A,
 }
 
 // ---------------------------------------------------------------------------
-// Tile selection.  ORCH_GEMM_TILE=<index> forces a configuration (tuning).
+// Tile selection.  ORCH_GEMM_TILE=<index> forces a configuration (tuning): a row
+// of kTiles, then of kSmall.
 struct TileCfg {
   int bm, bn, bk, waves, stages;
   float eff;  // measured relative throughput of the shape on a full machine
@@ -1078,6 +1198,77 @@ static void launch_tile_cfg(int c, const void* A, const void* W, int M, int N, i
   }
 }
 
+template <int BM, int BN, int KG, int U, int S, int EPI>
+static void launch_small_tile(const void* A, const void* W, int M, int N, int K, const EpiParams& ep0, hipStream_t s) {
+  using G = GemmSmallGeo<BM, BN, KG, U, S>;
+  EpiParams ep = ep0;
+  if (EPI == kEpiQkv) ep.hd_magic = (unsigned)((0x100000000ull + ep.head_dim - 1) / ep.head_dim);
+  auto kern = gemm_bf16_small_kernel<BM, BN, KG, U, S, EPI>;
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, G::LDS);
+  (void)attr;
+  hipLaunchKernelGGL(kern, dim3(ceil_div(M, BM) * (N / BN)), dim3(256), G::LDS, s, reinterpret_cast<const bf16*>(A),
+                     reinterpret_cast<const bf16*>(W), M, N, K, N / BN, ep);
+}
+
+// Whether and how to use the small kernel: the configuration with the least
+// estimated time, if that is below the estimate of the tile and k-split chosen
+// otherwise.  Estimates in us over the k-tiles of 64, fitted to M from 32 to 3328
+// at the DiT projections of hidden 384, 768 and 1152:
+//   small  2.5 + KT max(b, c WGs / 256): b a lone workgroup's k-tile, c what a CU
+//          needs per workgroup's k-tile when several share it (about 54 B per
+//          ns and CU of operands from L2, the same for all of them); one
+//          workgroup per CU (LDS): 2.5 + KT b rounds + 1.5 per further round
+//   128^2  4.5 + 0.42 KT / splits a round, plus 5 and 8 B of partials per split
+//          and output at 6 TB/s with a k-split
+// Measured, us before -> after: hidden 384, M = 96: qkv 5.3 -> 3.6, out-proj 6.5 -> 3.7,
+// fc1 6.3 -> 3.8, fc2 12.1 -> 5.5 (k-split and reduction before); hidden 1152, M =
+// 384: 14.7 -> 11.7, 13.5 -> 7.4, 16.1 -> 13.0, 25.2 -> 18.6; M = 768: out-proj 15.2 -> 9.1,
+// while qkv and fc1 stay (11.6 against 19.8, 13.3 against 23.4).
+struct SmallCfg {
+  int bm, bn, groups, k;   // k: K is a multiple of it
+  bool one;                // one workgroup per CU
+  float b, c;
+};
+static const SmallCfg kSmall[] = {
+    {32, 32, 4, 64, true, 0.125f, 0.0f}, {32, 32, 4, 64, false, 0.165f, 0.21f}, {32, 64, 2, 64, false, 0.205f, 0.25f},
+    {64, 64, 1, 128, true, 0.28f, 0.0f}, {64, 64, 1, 128, false, 0.33f, 0.38f},
+};
+
+static int pick_small(int M, int N, int K, const TileCfg& t, int splits, bool fixed_order) {
+  constexpr int n = sizeof(kSmall) / sizeof(kSmall[0]);
+  const int f = forced_tile();
+  if (f >= 0) return f >= kNumTiles && f < kNumTiles + n && K % kSmall[f - kNumTiles].k == 0 ? f - kNumTiles : -1;
+  const float kt = K / 64.0f;
+  const int rounds = ceil_div(ceil_div(M, t.bm) * (N / t.bn) * splits, 256);
+  if (t.bm != 128 || rounds > 1) return -1;
+  float best = 4.5f + 0.42f * kt / splits + (splits > 1 ? 5.0f + splits * ((float)M * N * 8e-6f / 6.0f) : 0.0f);
+  int pick = -1;
+  for (int i = 0; i < n; ++i) {
+    const SmallCfg& c = kSmall[i];
+    if (K % c.k || (fixed_order && c.groups > 1)) continue;
+    const int wgs = ceil_div(M, c.bm) * (N / c.bn), r = ceil_div(wgs, 256);
+    const float per = c.c * wgs / 256.0f;
+    const float us = c.one ? 2.5f + kt * c.b * r + 1.5f * (r - 1) : 2.5f + kt * (per > c.b ? per : c.b);
+    if (us < best) {
+      best = us;
+      pick = i;
+    }
+  }
+  return pick;
+}
+
+template <int EPI>
+static void launch_small(int c, const void* A, const void* W, int M, int N, int K, const EpiParams& ep, hipStream_t s) {
+  switch (c) {
+    case 0: launch_small_tile<32, 32, 4, 1, 4, EPI>(A, W, M, N, K, ep, s); break;
+    case 1: launch_small_tile<32, 32, 4, 1, 2, EPI>(A, W, M, N, K, ep, s); break;
+    case 2: launch_small_tile<32, 64, 2, 1, 3, EPI>(A, W, M, N, K, ep, s); break;
+    case 3: launch_small_tile<64, 64, 1, 2, 4, EPI>(A, W, M, N, K, ep, s); break;
+    default: launch_small_tile<64, 64, 1, 2, 2, EPI>(A, W, M, N, K, ep, s); break;
+  }
+}
+
 template <int BM, int BN, int KG, int S, int EPI>
 static void launch_f32_tile(const void* A, const void* W, int M, int N, int K, const EpiParams& ep, hipStream_t s) {
   using G = GemmF32Geo<BM, BN, KG, S>;
@@ -1113,7 +1304,10 @@ static hipError_t launch_gemm_epi(const void* A, const void* W, int M, int N, in
   if (mfma_path_ok(A, W, N, K, EPI, ep, dtype)) {
     const int c = pick_tile(M, N, K);
     const int sp = ep.ws && aligned16(ep.ws) ? split_plan(M, N, K, kTiles[c], ep.ws_elems) : 1;
-    if (sp > 1) {
+    const int sm = pick_small(M, N, K, kTiles[c], sp, ep.fixed_order);
+    if (sm >= 0) {
+      launch_small<EPI>(sm, A, W, M, N, K, ep, s);
+    } else if (sp > 1) {
       launch_tile_cfg<kEpiPartial>(c, A, W, M, N, K, ep, s, sp);
       hipLaunchKernelGGL((gemm_split_reduce_kernel<bf16, EPI>), dim3(ceil_div(N, 256), ceil_div(M, 4)),
                          dim3(256), 0, s, sp, M, N, ep);
