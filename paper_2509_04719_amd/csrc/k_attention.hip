@@ -809,6 +809,7 @@ static void launch_mfma(dim3 grid, const AttnParams& p, hipStream_t s) {
 hipError_t launch_attention(const AttnParams& p0, int dtype, hipStream_t s) {
   if (p0.n_q <= 0) return hipSuccess;
   AttnParams p = p0;
+  if (attention_general_better(p, dtype)) return launch_attention_general(p, dtype, s);
   // the MFMA kernel moves 16-byte chunks of Q, K and V^T (8 keys of V^T at a
   // time, all fresh or all stale)
   const bool aligned = p.fresh_begin % 8 == 0 && p.n_fresh % 8 == 0 && aligned16(p.q) &&

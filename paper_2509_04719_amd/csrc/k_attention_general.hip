@@ -389,7 +389,7 @@ __global__ __launch_bounds__(256, D * sizeof(T) >= 384 ? 1 : 2) void attn_genera
 bool attention_general_ok(const AttnParams& p, int dtype) {
   const int epc = dtype == kBF16 ? 8 : 4;
   auto a16 = [](const void* q) { return ((uintptr_t)q & 15) == 0; };
-  if (dtype == kBF16 && !(p.d == 32 || p.d == 80 || p.d == 96 || p.d == 128)) return false;
+  if (dtype == kBF16 && !(p.d == 32 || p.d == 64 || p.d == 80 || p.d == 96 || p.d == 128)) return false;
   if (p.n_kv % gen_attn::BKV || (long long)p.n_kv * p.d >= (1ll << 31)) return false;
   if (!a16(p.q) || !a16(p.kv_stale) || !a16(p.out) || p.stale_bs % epc) return false;
   return p.n_fresh == 0 ||
@@ -408,24 +408,38 @@ static hipError_t launch_kg(const AttnParams& p, hipStream_t s) {
   return hipGetLastError();
 }
 
+// bf16 heads of 64 channels: the other kernel's 128-query tiles leave CUs idle
+// where queries are few and walk all keys in one chain where those are too few
+// to cut (or merge the parts in a second launch).  Measured here / there, us: 6
+// heads, 96 queries x 256 keys 5.2 / 7.2, x 576 7.3 / 10.8, x 1024 9.3 / 11.5, x 2304
+// 16.2 / 16.0; 24 (branch, head) x 576 queries (432 waves) x 1024 keys 14.3 / 17.1; 32 x
+// 576 queries (576 waves) x 576 keys 12.9 / 11.7.
+bool attention_general_better(const AttnParams& p, int dtype) {
+  return dtype == kBF16 && p.d == 64 && !p.fixed_order && p.n_kv <= 1024 &&
+         (long long)ceil_div(p.n_q, 32) * p.heads * p.B <= 512 && attention_general_ok(p, dtype);
+}
+
 // Key groups per workgroup.  A wave of 32 queries is bound by its own chain
-// (0.8 us per 32 keys at d = 128), so keys are split until every SIMD of the
-// 1024 has a wave, two where a CU's LDS holds two such workgroups; past that a
-// split only shares each K/V tile among fewer queries.  Measured with 1 / 2 / 4
-// groups, us: bf16 d = 80, 64 waves x 4096 keys 90 / 47 / 31; 512 waves x 1024
-// keys 27.4 / 17.4 / 23.5; 1024 waves 29.8 / 25.7 / 44.9; 2048 waves 44.7 / 47.5 /
-// 87.0; d = 128 (one workgroup of two groups per CU), 512 waves 31.7 / 21.7, 1024
-// waves 35.7 / 42.4; fp32 d = 72, 512 waves 93 / 53, 1024 waves 96 / 103.
+// (0.8 us per 32 keys at d = 128), so the keys are split as far as all
+// workgroups stay resident at once; past that a split only shares each K/V tile
+// among fewer queries.  Measured with 1 / 2 / 4 groups, us: bf16 d = 80 (two
+// workgroups of two groups a CU, one of four), 256 waves x 1024 keys 26.3 / 15.7 /
+// 12.2; 512 waves 27.4 / 17.4 / 23.5; 1024 waves 29.8 / 25.7 / 44.9; 2048 waves 44.7 /
+// 47.5 / 87.0; d = 128 (one of two groups), 512 waves 31.7 / 21.7, 1024 waves 35.7 /
+// 42.4; fp32 d = 72 (one of two groups), 512 waves 93 / 53, 1024 waves 96 / 103.
+template <typename T, int D, int KG>
+static bool resident(const AttnParams& p) {
+  using G = gen_attn::Geo<T, D, KG>;
+  if (!G::FITS || p.fixed_order || p.n_kv / gen_attn::BKV < KG) return false;   // a tile for every group
+  return (long long)ceil_div(p.n_q, 32 * G::QG) * p.heads * p.B <= 256 * (160 * 1024 / G::LDS);
+}
+
 template <typename T, int D>
 static hipError_t launch_d(const AttnParams& p, hipStream_t s) {
-  using G2 = gen_attn::Geo<T, D, 2>;
-  using G4 = gen_attn::Geo<T, D, 4>;
-  const long long waves = (long long)ceil_div(p.n_q, 32) * p.heads * p.B;
-  const int nt = p.n_kv / gen_attn::BKV;     // a key group takes at least one tile
-  if constexpr (G4::FITS)
-    if (!p.fixed_order && waves < 512 && nt >= 4) return launch_kg<T, D, 4>(p, s);
-  if constexpr (G2::FITS)
-    if (!p.fixed_order && waves < (2 * G2::LDS <= 160 * 1024 ? 2048 : 1024) && nt >= 2) return launch_kg<T, D, 2>(p, s);
+  if constexpr (gen_attn::Geo<T, D, 4>::FITS)
+    if (resident<T, D, 4>(p)) return launch_kg<T, D, 4>(p, s);
+  if constexpr (gen_attn::Geo<T, D, 2>::FITS)
+    if (resident<T, D, 2>(p)) return launch_kg<T, D, 2>(p, s);
   return launch_kg<T, D, 1>(p, s);
 }
 
@@ -433,6 +447,7 @@ hipError_t launch_attention_general(const AttnParams& p, int dtype, hipStream_t 
   if (dtype == kBF16) {
     switch (p.d) {
       case 32: return launch_d<bf16, 32>(p, s);
+      case 64: return launch_d<bf16, 64>(p, s);
       case 80: return launch_d<bf16, 80>(p, s);
       case 96: return launch_d<bf16, 96>(p, s);
       case 128: return launch_d<bf16, 128>(p, s);

@@ -89,9 +89,11 @@ struct AttnParams {
 size_t attention_workspace_bytes(int B, int heads, int n_q, int n_kv, int d, int dtype);
 hipError_t launch_attention(const AttnParams& p, int dtype, hipStream_t stream);
 bool attention_uses_mfma(int d, int n_kv, int dtype);
-// bf16 heads of 32, 80, 96 and 128 channels and every fp32 head size, where
-// alignment and key count allow (k_attention_general.hip).
+// bf16 heads of 32, 64, 80, 96 and 128 channels and every fp32 head size, where
+// alignment and key count allow (k_attention_general.hip); _better: where it
+// beats the 64-channel instance of the other kernel.
 bool attention_general_ok(const AttnParams& p, int dtype);
+bool attention_general_better(const AttnParams& p, int dtype);
 hipError_t launch_attention_general(const AttnParams& p, int dtype, hipStream_t stream);
 
 // Conditioning.  temb: fp32 [H] scratch; sc: fp32 [B][H] SiLU(c);
