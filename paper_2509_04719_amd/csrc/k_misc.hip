@@ -158,44 +158,88 @@ hipError_t launch_layernorm_modulate(const float* x, int rows, int hidden, int r
 
 // ---------------------------------------------------------------------------
 // Conditioning.
+// 16 bytes of T as floats
+template <typename T>
+__device__ __forceinline__ void unpack16(const uint4& q, float* v) {
+  const unsigned w[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    if constexpr (sizeof(T) == 2) {
+      v[2 * e] = __uint_as_float(w[e] << 16);
+      v[2 * e + 1] = __uint_as_float(w[e] & 0xFFFF0000u);
+    } else {
+      v[e] = __uint_as_float(w[e]);
+    }
+  }
+}
+
 // t1[n] = SiLU(W1[n] . sinusoid(t) + b1[n]); sinusoid = [cos(t f_i), sin(t f_i)],
-// f_i = 10000^(-i/half), evaluated in double.  One wave per output row.
+// f_i = 10000^(-i/half), evaluated in double.  One wave per output row, four rows
+// a workgroup, whose threads share the sinusoid's evaluation (each wave for
+// itself: 5.6 us at hidden 1152, now 4.9).
+constexpr int kSinusoid = 1024;    // values held at a time
+
 template <typename T>
 __global__ __launch_bounds__(256) void temb1_kernel(const T* __restrict__ w1,
                                                     const float* __restrict__ b1, float t, int H,
                                                     int freq, float* __restrict__ t1) {
+  __shared__ float sinusoid[kSinusoid];
   const int n = blockIdx.x * 4 + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
-  if (n >= H) return;
   const int half = freq / 2;
+  const T* row = w1 + (size_t)min(n, H - 1) * freq;
   float acc = 0.0f;
-  for (int k = lane; k < freq; k += 64) {
-    const int i = k < half ? k : k - half;
-    const double f = exp(-9.210340371976184 * (double)i / (double)half);  // ln(10000)
-    const double a = (double)t * f;
-    const float e = (float)(k < half ? cos(a) : sin(a));
-    acc = fmaf(to_f<T>(w1[(size_t)n * freq + k]), e, acc);
+  for (int k0 = 0; k0 < freq; k0 += kSinusoid) {
+    const int m = min(freq - k0, kSinusoid);
+    if (k0 > 0) __syncthreads();
+    for (int j = threadIdx.x; j < m; j += 256) {
+      const int k = k0 + j, i = k < half ? k : k - half;
+      const double f = exp(-9.210340371976184 * (double)i / (double)half);  // ln(10000)
+      const double a = (double)t * f;
+      sinusoid[j] = (float)(k < half ? cos(a) : sin(a));
+    }
+    __syncthreads();
+    for (int j = lane; j < m; j += 64) acc = fmaf(to_f<T>(row[k0 + j]), sinusoid[j], acc);
   }
   acc = wave_sum(acc);
-  if (lane == 0) t1[n] = silu_f(acc + b1[n]);
+  if (n < H && lane == 0) t1[n] = silu_f(acc + b1[n]);
 }
 
-// sc[b][n] = SiLU(W2[n] . t1 + b2[n] + table[label_b][n]).
+// sc[b][n] = SiLU(W2[n] . t1 + b2[n] + table[label_b][n]).  One wave per row, in
+// 16-byte chunks, every load of the row in flight before the first is used (2
+// bytes a lane and load: 10.6 us at hidden 1152, now 4.7).
+constexpr int kTemb2Chunks = 8;    // H <= 2048: 512 chunks of four floats, 64 lanes
+
 template <typename T>
 __global__ __launch_bounds__(256) void temb2_kernel(const T* __restrict__ w2,
                                                     const float* __restrict__ b2,
                                                     const float* __restrict__ t1,
                                                     const T* __restrict__ table, int H, int B,
                                                     int lab0, int lab1, float* __restrict__ sc) {
+  constexpr int CH = 16 / sizeof(T);
   const int n = blockIdx.x * 4 + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   if (n >= H) return;
+  const uint4* row = reinterpret_cast<const uint4*>(w2 + (size_t)n * H);
+  const int nck = H / CH;
+  const float add0 = b2[n], y0 = to_f<T>(table[(size_t)lab0 * H + n]), y1 = to_f<T>(table[(size_t)lab1 * H + n]);
+  uint4 q[kTemb2Chunks];
+#pragma unroll
+  for (int u = 0; u < kTemb2Chunks; ++u)
+    if (lane + 64 * u < nck) q[u] = row[lane + 64 * u];
   float acc = 0.0f;
-  for (int k = lane; k < H; k += 64) acc = fmaf(to_f<T>(w2[(size_t)n * H + k]), t1[k], acc);
-  acc = wave_sum(acc) + b2[n];
+#pragma unroll
+  for (int u = 0; u < kTemb2Chunks; ++u)
+    if (lane + 64 * u < nck) {
+      float wv[CH];
+      unpack16<T>(q[u], wv);
+#pragma unroll
+      for (int e = 0; e < CH; ++e) acc = fmaf(wv[e], t1[(lane + 64 * u) * CH + e], acc);
+    }
+  acc = wave_sum(acc) + add0;
   if (lane == 0) {
-    sc[n] = silu_f(acc + to_f<T>(table[(size_t)lab0 * H + n]));
-    if (B > 1) sc[H + n] = silu_f(acc + to_f<T>(table[(size_t)lab1 * H + n]));
+    sc[n] = silu_f(acc + y0);
+    if (B > 1) sc[H + n] = silu_f(acc + y1);
   }
 }
 
@@ -207,7 +251,15 @@ __global__ __launch_bounds__(256) void temb2_kernel(const T* __restrict__ w2,
 // (both guidance branches) sits in LDS and is read as a broadcast.
 constexpr int kAdaGroup = 64;
 
-template <typename T>
+template <bool NT>
+__device__ __forceinline__ uint4 load16(const uint4* p) {
+  if constexpr (!NT) return *p;
+  typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+  const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
+  return make_uint4(v[0], v[1], v[2], v[3]);
+}
+
+template <typename T, bool NT>
 __global__ __launch_bounds__(256) void adaln_gemv_kernel(const T* __restrict__ w,
                                                          const float* __restrict__ bias,
                                                          const float* __restrict__ sc, int H,
@@ -231,23 +283,13 @@ __global__ __launch_bounds__(256) void adaln_gemv_kernel(const T* __restrict__ w
   for (int k0 = 0; k0 < nck; k0 += U) {
     uint4 q[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) q[u] = k0 + u < nck ? wg[(size_t)(k0 + u) * kAdaGroup] : make_uint4(0, 0, 0, 0);
+    for (int u = 0; u < U; ++u) q[u] = k0 + u < nck ? load16<NT>(wg + (size_t)(k0 + u) * kAdaGroup) : make_uint4(0, 0, 0, 0);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int k = k0 + u;
       if (k < nck) {
         float wv[CH];
-        if constexpr (sizeof(T) == 2) {
-          const unsigned wd[4] = {q[u].x, q[u].y, q[u].z, q[u].w};
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            wv[2 * e] = __uint_as_float(wd[e] << 16);
-            wv[2 * e + 1] = __uint_as_float(wd[e] & 0xFFFF0000u);
-          }
-        } else {
-          wv[0] = __uint_as_float(q[u].x); wv[1] = __uint_as_float(q[u].y);
-          wv[2] = __uint_as_float(q[u].z); wv[3] = __uint_as_float(q[u].w);
-        }
+        unpack16<T>(q[u], wv);
 #pragma unroll
         for (int e4 = 0; e4 < CH / 4; ++e4) {
           const float4 x0 = xs[(k * CH) / 4 + e4], x1 = xs[H / 4 + (k * CH) / 4 + e4];
@@ -274,9 +316,14 @@ static hipError_t launch_cond_t(const CondParams& p, hipStream_t s) {
                      reinterpret_cast<const T*>(p.table), p.hidden, p.B, p.labels[0],
                      p.labels[1], p.sc);
   const int blocks = ceil_div(ceil_div(p.n_mod, kAdaGroup), 4);
-  hipLaunchKernelGGL(adaln_gemv_kernel<T>, dim3(blocks), dim3(256), 0, s,
-                     reinterpret_cast<const T*>(p.w_ada), p.b_ada, p.sc, p.hidden, p.n_mod, p.B,
-                     p.mod);
+  // Weights that the 256 MB cache behind the L2s cannot hold to the next step are
+  // read past it.  Plain / non-temporal, us a call: 446 MB 91.5 / 79.2 (6.8 TB/s at
+  // best for reads alone on this card), 319 MB 70.6 / 65.8, 223 MB 42.1 / 44.6, 127 MB
+  // 33.6 / 39.8.
+  const bool past = (size_t)p.n_mod * p.hidden * sizeof(T) > ((size_t)256 << 20);
+  const auto gemv = past ? adaln_gemv_kernel<T, true> : adaln_gemv_kernel<T, false>;
+  hipLaunchKernelGGL(gemv, dim3(blocks), dim3(256), 0, s, reinterpret_cast<const T*>(p.w_ada), p.b_ada, p.sc,
+                     p.hidden, p.n_mod, p.B, p.mod);
   return hipGetLastError();
 }
 
@@ -294,31 +341,50 @@ hipError_t launch_conditioning(const CondParams& p, int dtype, hipStream_t s) {
 // ---------------------------------------------------------------------------
 // Patch embedding of the band: h[b][tok][n] = W[n] . patch(tok) + bias[n]
 // + pos[global tok][n], patch vector ordered (channel, dy, dx).  The weight is
-// held transposed, wt[k][n], so a block's threads read it coalesced.
+// held transposed, wt[k][n]; a thread owns four features (16-byte loads and
+// stores) of kPatchTok tokens, whose position rows are all in flight at once.
+// Bound by the rows it writes: 1664 tokens x 2 branches x 1152 took 15.9 us with
+// one feature a thread, 9.1 us now (23 MB).
 constexpr int kPatchTok = 4;  // tokens per thread
 
 // (patch 2, 4 channels: a 16-element patch vector, index k = c*4 + dy*2 + dx)
-__global__ __launch_bounds__(128) void patch_embed_kernel(PatchEmbedParams p) {
-  const int n = blockIdx.y * 128 + threadIdx.x;  // output feature
-  if (n >= p.hidden) return;
-  float wk[16];
+__global__ __launch_bounds__(64) void patch_embed_kernel(PatchEmbedParams p) {
+  const int q = blockIdx.y * 64 + threadIdx.x, Q = p.hidden / 4;  // feature quad
+  if (q >= Q) return;
+  const int n_tok = p.n_rows * p.grid, tok0 = blockIdx.x * kPatchTok;
+  const float4* pos = reinterpret_cast<const float4*>(p.pos);
+  const float4* w = reinterpret_cast<const float4*>(p.w);
+  float4 acc[kPatchTok], ps[kPatchTok];
+  const float4 bias = reinterpret_cast<const float4*>(p.b)[q];
 #pragma unroll
-  for (int k = 0; k < 16; ++k) wk[k] = p.w[(size_t)k * p.hidden + n];
-  const float bias = p.b[n];
-  const int n_tok = p.n_rows * p.grid;
   for (int u = 0; u < kPatchTok; ++u) {
-    const int tok = blockIdx.x * kPatchTok + u;    // band-local token
-    if (tok >= n_tok) break;
-    const int i = tok / p.grid, j = tok - (tok / p.grid) * p.grid;
-    const int gi = p.row_begin + i;
-    float acc = bias;
+    const int tok = min(tok0 + u, n_tok - 1);
+    ps[u] = pos[((size_t)p.row_begin * p.grid + tok) * Q + q];
+    acc[u] = bias;
+  }
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      const int c = k >> 2, dy = (k >> 1) & 1, dx = k & 1;
-      acc = fmaf(wk[k], p.x[((size_t)c * p.latent + gi * 2 + dy) * p.latent + j * 2 + dx], acc);
+  for (int k = 0; k < 16; ++k) {
+    const float4 wk = w[(size_t)k * Q + q];
+    const int c = k >> 2, dy = (k >> 1) & 1, dx = k & 1;
+#pragma unroll
+    for (int u = 0; u < kPatchTok; ++u) {
+      const int tok = min(tok0 + u, n_tok - 1);
+      const int i = tok / p.grid, j = tok - i * p.grid;
+      const float x = p.x[((size_t)c * p.latent + (p.row_begin + i) * 2 + dy) * p.latent + j * 2 + dx];
+      acc[u].x = fmaf(wk.x, x, acc[u].x);
+      acc[u].y = fmaf(wk.y, x, acc[u].y);
+      acc[u].z = fmaf(wk.z, x, acc[u].z);
+      acc[u].w = fmaf(wk.w, x, acc[u].w);
     }
-    acc += p.pos[((size_t)gi * p.grid + j) * p.hidden + n];
-    for (int b = 0; b < p.B; ++b) p.h[((size_t)b * n_tok + tok) * p.hidden + n] = acc;
+  }
+#pragma unroll
+  for (int u = 0; u < kPatchTok; ++u) {
+    const int tok = tok0 + u;
+    if (tok >= n_tok) break;
+    // (h may be a caller's buffer on 4 bytes)
+    typedef float row4 __attribute__((ext_vector_type(4), aligned(4)));
+    const row4 o = {acc[u].x + ps[u].x, acc[u].y + ps[u].y, acc[u].z + ps[u].z, acc[u].w + ps[u].w};
+    for (int b = 0; b < p.B; ++b) reinterpret_cast<row4*>(p.h)[((size_t)b * n_tok + tok) * Q + q] = o;
   }
 }
 
@@ -326,29 +392,72 @@ hipError_t launch_patch_embed(const PatchEmbedParams& p, hipStream_t s) {
   const int n_tok = p.n_rows * p.grid;
   if (n_tok <= 0) return hipSuccess;
   if (p.patch != 2 || p.C != 4) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(patch_embed_kernel, dim3(ceil_div(n_tok, kPatchTok), ceil_div(p.hidden, 128)),
-                     dim3(128), 0, s, p);
+  hipLaunchKernelGGL(patch_embed_kernel, dim3(ceil_div(n_tok, kPatchTok), ceil_div(p.hidden / 4, 64)),
+                     dim3(64), 0, s, p);
   return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
-// Final linear + unpatchify: one wave per (branch, token); output vector
-// ordered (dy, dx, channel) -> eps[b][c][i*p + dy][j*p + dx].
-template <typename T, int NO>
-__global__ __launch_bounds__(256) void final_linear_kernel(FinalParams p) {
+// Final linear + unpatchify; output vector ordered (dy, dx, channel) ->
+// eps[b][c][i*p + dy][j*p + dx].
+__device__ __forceinline__ void unpatchify_store(const FinalParams& p, int b, int tok, int o, float v) {
+  const int pp = p.patch;
+  const int c = o % p.out_ch;
+  const int dxy = o / p.out_ch;
+  const int dy = dxy / pp, dx = dxy - (dxy / pp) * pp;
+  const int i = tok / p.grid, j = tok - (tok / p.grid) * p.grid;
+  const int rows = p.n_rows * pp, W = p.grid * pp;
+  p.eps[(((size_t)b * p.out_ch + c) * rows + i * pp + dy) * W + j * pp + dx] = v;
+}
+
+// bf16, 16 outputs: a wave takes 16 tokens x 16 outputs on v_mfma_f32_16x16x32_bf16,
+// its operands straight from memory in 16-byte fragments (token, then output,
+// lane & 15, channels 8 (lane >> 4) .. + 8), kFinalBatch steps of them in flight.
+// (One token a wave in 2-byte loads: 17 us at 3328 tokens x 1152, now 6.8.)
+constexpr int kFinalBatch = 12;
+
+__global__ __launch_bounds__(64) void final_linear_mfma_kernel(FinalParams p) {
+  const int lane = threadIdx.x, r16 = lane & 15, g = lane >> 4;
+  const int total = p.B * p.n_tok, t0 = blockIdx.x * 16;
+  const bf16* u = reinterpret_cast<const bf16*>(p.u) + (size_t)min(t0 + r16, total - 1) * p.hidden + 8 * g;
+  const bf16* w = reinterpret_cast<const bf16*>(p.w) + (size_t)r16 * p.hidden + 8 * g;
+  f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+  for (int k0 = 0; k0 < p.hidden; k0 += 32 * kFinalBatch) {
+    bf16x8 a[kFinalBatch], x[kFinalBatch];
+#pragma unroll
+    for (int s = 0; s < kFinalBatch; ++s)
+      if (k0 + 32 * s < p.hidden) {
+        a[s] = *reinterpret_cast<const bf16x8*>(w + k0 + 32 * s);
+        x[s] = *reinterpret_cast<const bf16x8*>(u + k0 + 32 * s);
+      }
+#pragma unroll
+    for (int s = 0; s < kFinalBatch; ++s)
+      if (k0 + 32 * s < p.hidden) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[s], x[s], acc, 0, 0, 0);
+  }
+  // the lane holds outputs 4 g .. + 4 of token r16
+  const int t = t0 + r16;
+  if (t >= total) return;
+  const int b = t / p.n_tok, tok = t - b * p.n_tok;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) unpatchify_store(p, b, tok, 4 * g + r, acc[r] + p.b[4 * g + r]);
+}
+
+// fp32: one wave per (branch, token).
+template <int NO>
+__global__ __launch_bounds__(256) void final_linear_f32_kernel(FinalParams p) {
   const int wid = blockIdx.x * 4 + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   if (wid >= p.B * p.n_tok) return;
   const int b = wid / p.n_tok, tok = wid - b * p.n_tok;
-  const T* u = reinterpret_cast<const T*>(p.u) + (size_t)wid * p.hidden;
-  const T* w = reinterpret_cast<const T*>(p.w);
+  const float* u = reinterpret_cast<const float*>(p.u) + (size_t)wid * p.hidden;
+  const float* w = reinterpret_cast<const float*>(p.w);
   float acc[NO];
 #pragma unroll
   for (int o = 0; o < NO; ++o) acc[o] = 0.0f;
   for (int k = lane; k < p.hidden; k += 64) {
-    const float uv = to_f<T>(u[k]);
+    const float uv = u[k];
 #pragma unroll
-    for (int o = 0; o < NO; ++o) acc[o] = fmaf(to_f<T>(w[(size_t)o * p.hidden + k]), uv, acc[o]);
+    for (int o = 0; o < NO; ++o) acc[o] = fmaf(w[(size_t)o * p.hidden + k], uv, acc[o]);
   }
 #pragma unroll
   for (int o = 0; o < NO; ++o) acc[o] = wave_sum(acc[o]);
@@ -357,26 +466,18 @@ __global__ __launch_bounds__(256) void final_linear_kernel(FinalParams p) {
 #pragma unroll
     for (int o = 0; o < NO; ++o)
       if (o == lane) v = acc[o];
-    v += p.b[lane];
-    const int pp = p.patch;
-    const int c = lane % p.out_ch;
-    const int dxy = lane / p.out_ch;
-    const int dy = dxy / pp, dx = dxy - (dxy / pp) * pp;
-    const int i = tok / p.grid, j = tok - (tok / p.grid) * p.grid;
-    const int rows = p.n_rows * pp, W = p.grid * pp;
-    p.eps[(((size_t)b * p.out_ch + c) * rows + i * pp + dy) * W + j * pp + dx] = v;
+    unpatchify_store(p, b, tok, lane, v + p.b[lane]);
   }
 }
 
 hipError_t launch_final_linear(const FinalParams& p, int dtype, hipStream_t s) {
   const int total = p.B * p.n_tok;
   if (total <= 0) return hipSuccess;
-  if (p.out_ch * p.patch * p.patch != 16) return hipErrorInvalidValue;
-  dim3 grid(ceil_div(total, 4));
+  if (p.out_ch * p.patch * p.patch != 16 || p.hidden % 128) return hipErrorInvalidValue;
   if (dtype == kBF16)
-    hipLaunchKernelGGL((final_linear_kernel<bf16, 16>), grid, dim3(256), 0, s, p);
+    hipLaunchKernelGGL(final_linear_mfma_kernel, dim3(ceil_div(total, 16)), dim3(64), 0, s, p);
   else
-    hipLaunchKernelGGL((final_linear_kernel<float, 16>), grid, dim3(256), 0, s, p);
+    hipLaunchKernelGGL((final_linear_f32_kernel<16>), dim3(ceil_div(total, 4)), dim3(256), 0, s, p);
   return hipGetLastError();
 }
 
