@@ -6,7 +6,7 @@
 //
 // Three launches (four when the convolution splits its k-tiles):
 //   1. per-row partial sums (sum, sum of squares) of every channel group of
-//      the band's rows (one workgroup per row);
+//      the band's rows (one workgroup per row and slab of groups);
 //   2. the group statistics (mean, 1/sqrt(var + eps)) from every row's sums
 //      (float64 sums, taken by every workgroup of this launch), then
 //      SiLU(GroupNorm(x)) of the band, rounded to bf16, into a zero-bordered
@@ -28,23 +28,33 @@
 namespace orch {
 
 // ---------------------------------------------------------------------------
-// 1. Partial sums of one band row.  A thread owns one channel quad and walks
-// a share of the row's pixels (1024 threads: about a dozen shares, so each
-// thread has a few independent loads in flight); the shares meet in LDS and
-// are added in a fixed order (the sums are bitwise reproducible), then per
-// group.
-constexpr int kRowSumThreads = 1024;
+// 1. Partial sums of one band row, one workgroup per row and slab of channel
+// groups (at least 128 channels where the groups divide so; few rows then still
+// fill some CUs).  A thread owns one channel quad and walks a share of the row's
+// pixels, up to kRowSumBatch loads in flight; the shares meet in LDS and are
+// added in share order per channel, then per group by 16 lanes each, in an order
+// that C and G alone fix (the sums are bitwise reproducible).  Bound by latency:
+// 72 rows of 128 x 320 5.2 us as with one workgroup of 1024 threads per row before, 4 rows of
+// 32 x 1280 7.1 -> 4.5 us.
+constexpr int kRowSumThreads = 512;
 constexpr int kRowSumBatch = 12;
 
+// slabs of channel groups per row
+static int row_sum_slabs(int C, int G) {
+  for (int n = C / 128; n > 1; --n)
+    if (G % n == 0 && C / n % 4 == 0) return n;
+  return 1;
+}
+
 __global__ __launch_bounds__(kRowSumThreads) void gn_row_sums_kernel(UNetConvParams p) {
-  extern __shared__ float s_part[];          // [shares][C][2]
-  const int y = blockIdx.x;
-  const int C = p.C, W = p.W, Q = C / 4;
-  // Q <= threads: threads / Q pixel shares, one quad per thread; wider rows:
+  extern __shared__ float s_part[];          // [shares][slab channels][2]
+  const int y = blockIdx.x, slabs = gridDim.y;
+  const int CS = p.C / slabs, W = p.W, Q = CS / 4, QR = p.C / 4;   // channels of the slab; quads of it, of a pixel
+  // Q <= threads: threads / Q pixel shares, one quad per thread; wider slabs:
   // one share, a thread takes quads tid, tid + threads, ...
   const int per = Q <= kRowSumThreads ? kRowSumThreads / Q : 1;
   const int p0 = Q <= kRowSumThreads ? threadIdx.x / Q : 0;
-  const float4* row = reinterpret_cast<const float4*>(p.x + (size_t)y * W * C);
+  const float4* row = reinterpret_cast<const float4*>(p.x + (size_t)y * W * p.C) + blockIdx.y * Q;
   if (p0 < per) {
     for (int q = Q <= kRowSumThreads ? threadIdx.x % Q : threadIdx.x; q < Q;
          q += Q <= kRowSumThreads ? Q : kRowSumThreads) {
@@ -54,7 +64,7 @@ __global__ __launch_bounds__(kRowSumThreads) void gn_row_sums_kernel(UNetConvPar
         float4 v[kRowSumBatch];
 #pragma unroll
         for (int i = 0; i < kRowSumBatch; ++i)
-          if (x0 + i * per < W) v[i] = row[(size_t)(x0 + i * per) * Q + q];
+          if (x0 + i * per < W) v[i] = row[(size_t)(x0 + i * per) * QR + q];
 #pragma unroll
         for (int i = 0; i < kRowSumBatch; ++i)
           if (x0 + i * per < W) {
@@ -62,7 +72,7 @@ __global__ __launch_bounds__(kRowSumThreads) void gn_row_sums_kernel(UNetConvPar
             ss[0] += v[i].x * v[i].x; ss[1] += v[i].y * v[i].y; ss[2] += v[i].z * v[i].z; ss[3] += v[i].w * v[i].w;
           }
       }
-      float* dst = s_part + (size_t)p0 * 2 * C + 8 * q;
+      float* dst = s_part + (size_t)p0 * 2 * CS + 8 * q;
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         dst[2 * k] = s[k];
@@ -71,24 +81,34 @@ __global__ __launch_bounds__(kRowSumThreads) void gn_row_sums_kernel(UNetConvPar
     }
   }
   __syncthreads();
-  // channel totals over the shares (in share order) into share 0's slots,
-  // then group totals over the channels (in channel order)
-  for (int i = threadIdx.x; i < 2 * C; i += kRowSumThreads) {
+  // channel totals over the shares (in share order) into share 0's slots, then
+  // group totals: 16 lanes a group, lane l adding channels l, l + 16, ..., then
+  // the lanes' sums by halving
+  for (int i = threadIdx.x; i < 2 * CS; i += kRowSumThreads) {
     float a = s_part[i];
-    for (int k = 1; k < per; ++k) a += s_part[(size_t)k * 2 * C + i];
+    for (int k = 1; k < per; ++k) a += s_part[(size_t)k * 2 * CS + i];
     s_part[i] = a;
   }
   __syncthreads();
-  const int cg = C / p.G;
-  for (int g = threadIdx.x; g < p.G; g += kRowSumThreads) {
+  const int cg = p.C / p.G, gs = p.G / slabs, l16 = threadIdx.x & 15;
+  for (int g = threadIdx.x >> 4; g < (gs + 3) / 4 * 4; g += kRowSumThreads / 16) {   // (whole waves stay)
     float a = 0.0f, b = 0.0f;
-    for (int c = g * cg; c < (g + 1) * cg; ++c) {
-      a += s_part[2 * c];
-      b += s_part[2 * c + 1];
+    if (g < gs)
+      for (int c = g * cg + l16; c < (g + 1) * cg; c += 16) {
+        a += s_part[2 * c];
+        b += s_part[2 * c + 1];
+      }
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) {
+      a += __shfl_xor(a, o, 16);
+      b += __shfl_xor(b, o, 16);
     }
-    float2 v = make_float2(a, b);
-    reinterpret_cast<float2*>(p.fresh_sums)[(size_t)y * p.G + g] = v;
-    if (p.refresh) reinterpret_cast<float2*>(p.stale_sums)[(size_t)(p.row_begin + y) * p.G + g] = v;
+    if (g < gs && l16 == 0) {
+      const int gg = blockIdx.y * gs + g;
+      const float2 v = make_float2(a, b);
+      reinterpret_cast<float2*>(p.fresh_sums)[(size_t)y * p.G + gg] = v;
+      if (p.refresh) reinterpret_cast<float2*>(p.stale_sums)[(size_t)(p.row_begin + y) * p.G + gg] = v;
+    }
   }
 }
 
@@ -107,12 +127,21 @@ __device__ void group_stats(const UNetConvParams& p, float2* stats_lds) {
   const float2* fr = reinterpret_cast<const float2*>(p.fresh_sums);
   double s = 0.0, q = 0.0;
   if (part < per) {
-#pragma unroll 4
-    for (int y = part; y < p.H; y += per) {
-      const bool band = y >= p.row_begin && y < p.row_end;
-      const float2 v = band ? fr[(size_t)(y - p.row_begin) * p.G + g] : st[(size_t)y * p.G + g];
-      s += v.x;
-      q += v.y;
+    // sixteen rows' loads in flight, added in row order
+    for (int y0 = part; y0 < p.H; y0 += 16 * per) {
+      float2 v[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) {
+        const int y = y0 + u * per;
+        const bool band = y >= p.row_begin && y < p.row_end;
+        if (y < p.H) v[u] = *(band ? fr + (size_t)(y - p.row_begin) * p.G + g : st + (size_t)y * p.G + g);
+      }
+#pragma unroll
+      for (int u = 0; u < 16; ++u)
+        if (y0 + u * per < p.H) {
+          s += v[u].x;
+          q += v[u].y;
+        }
     }
   }
   red[t][0] = s;
@@ -142,7 +171,16 @@ __device__ void group_stats(const UNetConvParams& p, float2* stats_lds) {
 // column x + 1) and, on a refresh, to the band rows of the stale buffer.  The
 // tile's border follows: its first and last rows are the stale rows above
 // and below the band (zero outside the map), its first and last columns zero.
+// 72 rows of 128 x 320 with refresh: 11.5 us with one load in flight, an IEEE division
+// and an integer division per element, 9.7 us now (24 MB).
 constexpr int kSiluBlocks = 512;
+constexpr int kSiluBatch = 4;
+
+// x / (1 + e^-x) on v_exp_f32 and v_rcp_f32 (a few units of 2^-24; the result is
+// rounded to bf16)
+__device__ __forceinline__ float silu_fast(float x) {
+  return x * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(x * -1.4426950408889634f));
+}
 
 __global__ __launch_bounds__(256) void gn_silu_kernel(UNetConvParams p) {
   __shared__ float2 stats[256];
@@ -165,19 +203,29 @@ __global__ __launch_bounds__(256) void gn_silu_kernel(UNetConvParams p) {
   bf16x4* tile = reinterpret_cast<bf16x4*>(p.act_pad);
   bf16x4* band = p.refresh ? reinterpret_cast<bf16x4*>(p.stale_act) + (size_t)p.row_begin * W * Q : nullptr;
   const float inv_w = 1.0f / (float)W;
-  for (unsigned i = first; i < n4; i += stride) {
-    const float4 v = reinterpret_cast<const float4*>(p.x)[i];
-    const float xv[4] = {v.x, v.y, v.z, v.w};
-    bf16x4 o;
+  // the thread's quad of pixel px, px + dpx, ...: kSiluBatch loads in flight
+  const unsigned q = first % Q, dpx = stride / Q;
+  int px = (int)(first / Q);
+  for (unsigned i0 = first; i0 < n4; i0 += kSiluBatch * stride) {
+    float4 v[kSiluBatch];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) o[k] = (bf16)silu_f(fmaf(xv[k], mul[k], add[k]));
-    // band pixel px = (y, x) -> tile pixel (y + 1) (W + 2) + x + 1 = px + 2 y + W + 3
-    const int px = (int)(i / Q);
-    int y = (int)(((float)px + 0.5f) * inv_w);
-    y -= y * W > px;
-    y += (y + 1) * W <= px;
-    tile[(unsigned)(px + 2 * y + W + 3) * Q + (i - (unsigned)px * Q)] = o;
-    if (band) band[i] = o;
+    for (int u = 0; u < kSiluBatch; ++u)
+      if (i0 + u * stride < n4) v[u] = reinterpret_cast<const float4*>(p.x)[i0 + u * stride];
+#pragma unroll
+    for (int u = 0; u < kSiluBatch; ++u, px += dpx) {
+      const unsigned i = i0 + u * stride;
+      if (i >= n4) break;
+      const float xv[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+      bf16x4 o;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) o[k] = (bf16)silu_fast(fmaf(xv[k], mul[k], add[k]));
+      // band pixel px = (y, x) -> tile pixel (y + 1) (W + 2) + x + 1 = px + 2 y + W + 3
+      int y = (int)(((float)px + 0.5f) * inv_w);
+      y -= y * W > px;
+      y += (y + 1) * W <= px;
+      tile[(unsigned)(px + 2 * y + W + 3) * Q + q] = o;
+      if (band) band[i] = o;
+    }
   }
   // border: 2 (W + 2) Q quads of the halo rows, then 2 rows Q of the side columns
   const unsigned halo = 2u * (W + 2) * Q, nb = halo + 2u * rows * Q;
@@ -217,28 +265,27 @@ __global__ __launch_bounds__(256) void gn_silu_kernel(UNetConvParams p) {
 // rows at one logical chunk) hit distinct banks.  The MFMAs take the weight
 // rows as the first operand, so a lane ends with four consecutive output
 // channels of one pixel.  The main loop's emission order is fixed with
-// scheduling fences: each MFMA, then its share of the next k-step's fragment
-// reads, then its share of the next tile's loads.  The epilogue stages each
+// scheduling fences: each MFMA, then its share of the next k-tile's fragment
+// reads, then its share of the loads.  The epilogue stages each
 // wave's block in LDS and writes whole runs of a pixel's channels.  Launches
 // with few tiles split their k-tiles (tap, channel chunk) in even ranges over
 // more workgroups; the fp32 partial sums are added in order by a second
 // kernel, which adds the bias.
 namespace conv {
-constexpr int BM = 128, BK = 64;
+constexpr int BK = 64;
 constexpr int ROWB = 2 * BK;                         // bytes per LDS row
-// BN output channels per workgroup on WM x WN waves (wave tile TM pixels x
-// TN channels), MF x MF MFMA blocks (32: v_mfma_f32_32x32x16_bf16, 16:
+// BM pixels x BN output channels per workgroup on WM x WN waves (wave tile TM
+// pixels x TN channels), MF x MF MFMA blocks (32: v_mfma_f32_32x32x16_bf16, 16:
 // v_mfma_f32_16x16x32_bf16), a ring of S stages
-template <int BN_, int WM_, int WN_, int S_, int MF_>
+template <int BM_, int BN_, int WM_, int WN_, int S_, int MF_>
 struct Geo {
-  static constexpr int BN = BN_, WM = WM_, WN = WN_, NW = WM_ * WN_, S = S_, MF = MF_;
+  static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, NW = WM_ * WN_, S = S_, MF = MF_;
   static constexpr int TM = BM / WM, TN = BN / WN;
   static constexpr int FM = TM / MF, FN = TN / MF;     // MFMA blocks per wave
   static constexpr int KK = BK / (MF == 32 ? 16 : 32); // MFMA k-steps per k-tile
   static constexpr int STAGE = (BM + BN) * ROWB;
   static constexpr int SLABS_A = BM / 8, SLABS = (BM + BN) / 8;
   static constexpr int LPT = (SLABS + NW - 1) / NW;    // loads per lane per k-tile
-  static constexpr int LPK = (LPT + KK - 1) / KK;      // loads issued per k-step
   static constexpr int WPC = 160 * 1024 / (S * STAGE);  // workgroups per CU (LDS)
   static constexpr int SROW = TN + 4;                  // epilogue strip row (floats)
   static constexpr int CPR = TN / 4;                   // 16-byte chunks of a strip row
@@ -256,15 +303,15 @@ struct Geo {
 // 160 channels (widths divisible by 160 and not by 128, such as 320):
 // 36 KB stages, four, one workgroup of eight waves of 32 pixels x 80
 // channels on 16x16x32 MFMAs, so a 320-wide map is two tiles across
-using Narrow = Geo<64, 4, 1, 3, 32>;
-using Wide = Geo<128, 4, 2, 4, 32>;
-using Mid = Geo<160, 4, 2, 4, 16>;
+using Narrow = Geo<128, 64, 4, 1, 3, 32>;
+using Wide = Geo<128, 128, 4, 2, 4, 32>;
+using Mid = Geo<128, 160, 4, 2, 4, 16>;
 }
 
 template <class G>
 __global__ __launch_bounds__(64 * G::NW) void conv3x3_mfma_kernel(UNetConvParams p, int splits) {
   using namespace conv;
-  constexpr int NW = G::NW, S = G::S, STAGE = G::STAGE, LPT = G::LPT, LPK = G::LPK, KK = G::KK;
+  constexpr int BM = G::BM, NW = G::NW, S = G::S, STAGE = G::STAGE, LPT = G::LPT, KK = G::KK;
   constexpr int MF = G::MF, FM = G::FM, FN = G::FN, TM = G::TM, TN = G::TN, SROW = G::SROW, CPR = G::CPR;
   using Acc = std::conditional_t<MF == 32, f32x16, f32x4>;
   constexpr int AR = MF == 32 ? 16 : 4;                // accumulator registers
@@ -339,67 +386,90 @@ __global__ __launch_bounds__(64 * G::NW) void conv3x3_mfma_kernel(UNetConvParams
 #pragma unroll
   for (int kk = 0; kk < KK; ++kk) koff[kk] = (((64 / MF) * kk + fh) ^ ((frow >> 1) & 7)) * 16;
 
-  // the MFMAs of stage st; with ISSUE, k-tile ig's loads into stage ist go
-  // between them: MFMA e of k-step kk, its share of k-step kk + 1's
-  // fragment reads, its share of the loads
-  auto compute = [&](int st, auto issue_c, int ig, int ist) {
-    constexpr bool ISSUE = decltype(issue_c)::value;
-    constexpr int NM = FM * FN, ND = FM + FN;
-    const char* base = smem + st * STAGE;
-    const int ash = ISSUE ? a_shift(ig) : 0;
-    bf16x8 fa[2][FM], fb[2][FN];
-#pragma unroll
-    for (int i = 0; i < FM; ++i) fa[0][i] = *reinterpret_cast<const bf16x8*>(base + arow + i * MF * ROWB + koff[0]);
-#pragma unroll
-    for (int j = 0; j < FN; ++j) fb[0][j] = *reinterpret_cast<const bf16x8*>(base + brow + j * MF * ROWB + koff[0]);
-    __builtin_amdgcn_sched_barrier(0);
-    static_for<0, KK>([&](auto kkc) {
-      constexpr int kk = decltype(kkc)::value;
-      constexpr int cur = kk & 1, nk = kk + 1 < KK ? kk + 1 : kk;
-      constexpr int nd = kk + 1 < KK ? ND : 0;
-      constexpr int l0 = cmin(kk * LPK, LPT), nl = ISSUE ? cmin(kk * LPK + LPK, LPT) - l0 : 0;
-      static_for<0, NM>([&](auto ec) {
-        constexpr int e = decltype(ec)::value;
-        constexpr int i = e / FN, j = e % FN;
-        if constexpr (MF == 32)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[cur][j], fa[cur][i], acc[i][j], 0, 0, 0);
-        else
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[cur][j], fa[cur][i], acc[i][j], 0, 0, 0);
-        static_for<e * nd / NM, (e + 1) * nd / NM>([&](auto dc) {
-          constexpr int d = decltype(dc)::value;
-          if constexpr (d < FM)
-            fa[cur ^ 1][d] = *reinterpret_cast<const bf16x8*>(base + arow + d * MF * ROWB + koff[nk]);
-          else
-            fb[cur ^ 1][d - FM] = *reinterpret_cast<const bf16x8*>(base + brow + (d - FM) * MF * ROWB + koff[nk]);
-        });
-        static_for<l0 + e * nl / NM, l0 + (e + 1) * nl / NM>([&](auto jc) { dma(jc, ig, ash, ist); });
-        __builtin_amdgcn_sched_barrier(0);
-      });
+  // A k-tile's fragments are read a whole k-tile ahead, into the other of two
+  // register sets: the barrier of iteration kt publishes k-tile kt + 1 and frees
+  // the stage of k-tile kt, and between that k-tile's MFMAs go the reads of k-tile
+  // kt + 1 and the loads of k-tile kt + S.  (Reading one k-step ahead left each
+  // k-tile's first fragments waiting behind its barrier: whole calls, 320 channels,
+  // 56 / 72 / 90 / 128 rows of 128 pixels 39.4 / 45.1 / 48.2 / 54.5 us then, 38.1 / 42.1 /
+  // 44.5 / 51.6 now.)
+  constexpr int FR = FM + FN, ND = KK * FR, NM = FM * FN;
+  bf16x8 f[2][ND];
+  auto read = [&](int set, int d, int st) __attribute__((always_inline)) {
+    const int kk = d / FR, q = d % FR;
+    f[set][d] = *reinterpret_cast<const bf16x8*>(
+        smem + st * STAGE + (q < FM ? arow + q * MF * ROWB : brow + (q - FM) * MF * ROWB) + koff[kk]);
+  };
+  // k-tile kt from set SET; NEXT: k-tile kt + 1 is read, LOAD: k-tile kt + S is loaded
+  auto iterate = [&](auto set_c, auto next_c, auto load_c, int kt) __attribute__((always_inline)) {
+    constexpr int SET = decltype(set_c)::value;
+    constexpr bool NEXT = decltype(next_c)::value, LOAD = decltype(load_c)::value;
+    const int st = kt % S, nst = (kt + 1) % S, ash = LOAD ? a_shift(kt0 + kt + S) : 0;
+    static_for<0, KK * NM>([&](auto ec) {
+      constexpr int e = decltype(ec)::value, kk = e / NM, i = e % NM / FN, j = e % FN;
+      constexpr int fa = kk * FR + i, fb = kk * FR + FM + j;
+      if constexpr (MF == 32)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[SET][fb], f[SET][fa], acc[i][j], 0, 0, 0);
+      else
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[SET][fb], f[SET][fa], acc[i][j], 0, 0, 0);
+      if constexpr (NEXT)
+        static_for<e * ND / (KK * NM), (e + 1) * ND / (KK * NM)>([&](auto dc) { read(SET ^ 1, decltype(dc)::value, nst); });
+      if constexpr (LOAD)
+        static_for<e * LPT / (KK * NM), (e + 1) * LPT / (KK * NM)>([&](auto jc) { dma(jc, kt0 + kt + S, ash, st); });
+      __builtin_amdgcn_sched_barrier(0);
     });
   };
+  // k-tile kt + 1 landed (AHEAD k-tiles in flight behind it), every read done
+  auto sync = [&](auto ahead_c) __attribute__((always_inline)) {
+    wait_vmcnt<decltype(ahead_c)::value * LPT>();
+    __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
+    __builtin_amdgcn_sched_barrier(0);
+    lds_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+  };
 
-  // prologue: k-tiles 0 .. S - 2 (KT >= S - 1: at least four k-tiles a split)
+  // prologue: k-tiles 0 .. S - 1 (KT >= S: at least four k-tiles a split)
 #pragma unroll
-  for (int t = 0; t < S - 1; ++t) {
+  for (int t = 0; t < S; ++t) {
     const int ash = a_shift(kt0 + t);
     static_for<0, LPT>([&](auto jc) { dma(jc, kt0 + t, ash, t); });
   }
-  int kt = 0;
-  for (; kt + S - 1 < KT; ++kt) {
-    wait_vmcnt<(S - 2) * LPT>();
-    lds_barrier();
-    compute(kt % S, std::true_type{}, kt0 + kt + S - 1, (kt + S - 1) % S);
-  }
-  // drain: the last S - 1 k-tiles, nothing more to issue
-  static_for<0, S - 2>([&](auto rc) {
-    wait_vmcnt<(S - 2 - decltype(rc)::value) * LPT>();
-    lds_barrier();
-    compute(kt % S, std::false_type{}, 0, 0);
-    ++kt;
-  });
-  wait_vmcnt<0>();
+  wait_vmcnt<(S - 1) * LPT>();
   lds_barrier();
-  compute(kt % S, std::false_type{}, 0, 0);
+#pragma unroll
+  for (int d = 0; d < ND; ++d) read(0, d, 0);
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
+  using AHEAD = std::integral_constant<int, S - 2>;
+  int kt = 0;
+  for (; kt + S + 1 < KT; kt += 2) {
+    sync(AHEAD{});
+    iterate(I0{}, std::true_type{}, std::true_type{}, kt);
+    sync(AHEAD{});
+    iterate(I1{}, std::true_type{}, std::true_type{}, kt + 1);
+  }
+  // the last S k-tiles, or S + 1: one more load, then none
+  bool odd = false;
+  if (kt + S < KT) {
+    sync(AHEAD{});
+    iterate(I0{}, std::true_type{}, std::true_type{}, kt);
+    ++kt;
+    odd = true;
+  }
+  auto drain = [&](auto first_c) __attribute__((always_inline)) {
+    static_for<0, S>([&](auto rc) {
+      constexpr int r = decltype(rc)::value;
+      using SET = std::integral_constant<int, (decltype(first_c)::value + r) & 1>;
+      if constexpr (r + 1 < S) {
+        sync(std::integral_constant<int, S - 2 - r>{});
+        iterate(SET{}, std::true_type{}, std::false_type{}, kt + r);
+      } else {
+        iterate(SET{}, std::false_type{}, std::false_type{}, kt + r);
+      }
+    });
+  };
+  if (odd) drain(I1{});
+  else drain(I0{});
 
   // epilogue: through a per-wave strip [TM pixels][TN channels] in LDS.  With
   // 32x32 blocks a lane holds pixel 32 i + (lane & 31), channels 32 j + 8 g +
@@ -440,9 +510,16 @@ __global__ __launch_bounds__(256) void conv_split_reduce_kernel(UNetConvParams p
   const float4* part = reinterpret_cast<const float4*>(p.partial);
   for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n4; i += (size_t)gridDim.x * 256) {
     float4 v = reinterpret_cast<const float4*>(p.bias)[i % q4];
-    for (int sp = 0; sp < splits; ++sp) {
-      const float4 a = part[(size_t)sp * n4 + i];
-      v.x += a.x; v.y += a.y; v.z += a.z; v.w += a.w;
+    // eight splits' loads in flight (one after the other: 6.1 us for 16 splits of 128 x
+    // 1280, now 3.9)
+    for (int s0 = 0; s0 < splits; s0 += 8) {
+      float4 a[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (s0 + u < splits) a[u] = part[(size_t)(s0 + u) * n4 + i];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (s0 + u < splits) { v.x += a[u].x; v.y += a[u].y; v.z += a[u].z; v.w += a[u].w; }
     }
     reinterpret_cast<float4*>(p.out)[i] = v;
   }
@@ -460,8 +537,8 @@ __global__ __launch_bounds__(256) void conv_split_reduce_kernel(UNetConvParams p
 // mid 0.51: a lone workgroup's k-tile, and what the round's sharing of CUs
 // and bandwidth adds); a split adds the fp32 partials' round trip (written
 // by the convolution, added in order by the reduction kernel) at 0.43 us
-// per MB.  On those bands it picks plans within 3 us in total of the
-// fastest measured.
+// per MB.  On those bands it picks plans within 3 us each of the fastest
+// measured since.
 struct ConvPlan {
   int geo;     // 0: narrow, 1: wide, 2: mid
   int splits;
@@ -469,7 +546,7 @@ struct ConvPlan {
 
 template <class G>
 static ConvPlan conv_best_splits(int geo, double a, double b, int M, int C, int C_out, double* best_us) {
-  const int tiles = ceil_div(M, conv::BM) * (C_out / G::BN);
+  const int tiles = ceil_div(M, G::BM) * (C_out / G::BN);
   const int slots = 256 * G::WPC;
   const int kts = 9 * (C / conv::BK);
   const double mb = (double)M * C_out * sizeof(float) / 1e6;
@@ -511,7 +588,7 @@ static void launch_conv(const UNetConvParams& p, int M, int sp, hipStream_t s) {
     return true;
   }();
   (void)attr;
-  const int tiles = ceil_div(M, conv::BM) * (p.C_out / G::BN);
+  const int tiles = ceil_div(M, G::BM) * (p.C_out / G::BN);
   hipLaunchKernelGGL(kern, dim3(tiles * sp), dim3(64 * G::NW), G::S * G::STAGE, s, p, sp);
 }
 
@@ -537,9 +614,10 @@ hipError_t launch_unet_conv(const UNetConvParams& p0, void* ws, hipStream_t s) {
   p.act_pad = w;
   w += al256((size_t)(rows + 2) * (p.W + 2) * p.C * sizeof(bf16));
   p.partial = sp > 1 ? reinterpret_cast<float*>(w) : nullptr;
-  const int q4 = p.C / 4, shares = q4 <= kRowSumThreads ? kRowSumThreads / q4 : 1;
-  hipLaunchKernelGGL(gn_row_sums_kernel, dim3(rows), dim3(kRowSumThreads),
-                     (size_t)shares * 2 * p.C * sizeof(float), s, p);
+  const int slabs = row_sum_slabs(p.C, p.G), q4 = p.C / slabs / 4;
+  const int shares = q4 <= kRowSumThreads ? kRowSumThreads / q4 : 1;
+  hipLaunchKernelGGL(gn_row_sums_kernel, dim3(rows, slabs), dim3(kRowSumThreads),
+                     (size_t)shares * 8 * q4 * sizeof(float), s, p);
   // workgroups: enough for the band (at most kSiluBlocks), a multiple of
   // Q / gcd(Q, 256) so that 256 * blocks is a multiple of the C / 4 quads
   const size_t n4 = (size_t)rows * p.W * p.C / 4;
