@@ -270,12 +270,12 @@ enum {
 int orch_set_kernel_timing(orch_ctx* ctx, int enable);
 
 /* Work split of the step's kernels (default on).  On: GEMMs with too few
- * output tiles to fill the GPU split K over more workgroups, and attention
- * cuts query tiles between workgroups, whenever the context's workspace
- * allows (faster for short bands; the summation order then depends on the
- * band's height).  Off: every GEMM runs unsplit and every attention query
- * tile stays in one workgroup, so each output's summation order is fixed by
- * the token alone: bands stitched from a buffer holding the full step's K/V
+ * output tiles to fill the GPU split K over more waves or workgroups, and
+ * attention shares a query tile's keys between waves or workgroups, where
+ * that is faster (short bands; over workgroups as the context's workspace
+ * allows; the summation order then depends on the band's height).  Off:
+ * every GEMM output and every attention query is summed in one chain, so
+ * each output's summation order is fixed by the token alone: bands stitched from a buffer holding the full step's K/V
  * reproduce the all-rows step bit for bit.  Takes effect at the next step. */
 int orch_set_work_split(orch_ctx* ctx, int enable);
 int orch_kernel_times(orch_ctx* ctx, double* total_ms, long long* launches);
@@ -302,8 +302,9 @@ enum { ORCH_EPI_STORE = 0, ORCH_EPI_GELU = 1, ORCH_EPI_RESIDUAL = 2 };
  * workspace: device memory of at least orch_linear_workspace_bytes() bytes
  * (16-byte aligned) lets a GEMM with too few output tiles to fill the GPU
  * split K over more workgroups (fp32 partials, then a reduction that applies
- * the epilogue); NULL (or fewer bytes) runs unsplit.  The result does not
- * depend on the split beyond rounding. */
+ * the epilogue); NULL (or fewer bytes) runs without that split (waves of one
+ * workgroup may still share K).  The result does not depend on the split
+ * beyond rounding. */
 int orch_op_linear(const void* A, int M, int K, const void* W, int N, const float* bias,
                    int epilogue, const float* gate, int gate_stride, int rows_per_batch,
                    void* out, void* workspace, size_t workspace_bytes, int dtype,
@@ -331,8 +332,8 @@ int orch_op_qkv_projection(const void* A, int B, int n_tok, int K, const void* W
  * stride stale_branch_stride).  n_fresh may be 0.  out T [B][n_q][H].
  * workspace: device memory of at least orch_attention_workspace_bytes() bytes
  * lets short bands split the keys over more workgroups; NULL (or fewer
- * bytes) runs unsplit.  The result does not depend on the split beyond
- * rounding. */
+ * bytes) runs without that split (waves of one workgroup may still share the
+ * keys).  The result does not depend on the split beyond rounding. */
 int orch_op_attention(const void* q, const void* kv_stale, size_t stale_branch_stride,
                       const void* kv_fresh, size_t fresh_branch_stride, int fresh_begin,
                       int n_fresh, int B, int heads, int n_q, int n_kv, int head_dim, void* out,
