@@ -17,6 +17,9 @@
 //         MFMAs for each V^T fragment: 16 significant bits of p reach the PV
 //         product, so rounding the output to bf16 stays the only error that
 //         shows (2-norm against float64 1.7e-3; with p rounded once 2.4e-3).
+//         hi is p's top 16 bits and lo what is left of p (1 + 2^-23), so both are
+//         positive (down to p = 2^-103) and an infinite V gives hi V + lo V = V,
+//         not a NaN.
 // K tiles ([32 keys][d]) and V^T tiles ([d][32 keys]) go global -> LDS with the
 // direct-to-LDS load into a ring of stages, one barrier per iteration, their
 // 16-byte chunks swizzled by row so that 16 rows at one chunk hit distinct banks.
@@ -38,6 +41,7 @@ namespace orch {
 
 namespace gen_attn {
 constexpr int BKV = 32;
+constexpr float kUp = 1.0f + 0x1p-23f;
 
 constexpr int gcd_(int a, int b) { return b == 0 ? a : gcd_(b, a % b); }
 
@@ -253,8 +257,13 @@ __global__ __launch_bounds__(256, D * sizeof(T) >= 384 ? 1 : 2) void attn_genera
     auto take = [&](auto xc, int e) __attribute__((always_inline)) {
       constexpr int x = decltype(xc)::value;
       sum += pv[e];
-      hi[x & 1][e] = (T)pv[e];
-      if constexpr (!F32) lo[x & 1][e] = (T)(pv[e] - (float)hi[x & 1][e]);
+      if constexpr (F32) {
+        hi[x & 1][e] = pv[e];
+      } else {
+        const unsigned top = __float_as_uint(pv[e]) & 0xffff0000u;
+        hi[x & 1][e] = __builtin_bit_cast(bf16, (unsigned short)(top >> 16));
+        lo[x & 1][e] = (bf16)fmaf(pv[e], kUp, -__uint_as_float(top));
+      }
     };
     auto prob = [&](auto xc, int e) __attribute__((always_inline)) {
       constexpr int x = decltype(xc)::value;
