@@ -301,9 +301,10 @@ __global__ __launch_bounds__(256, D * sizeof(T) >= 384 ? 1 : 2) void attn_genera
   };
 
   // Key group kg's tiles kg, kg + KG, ...; the groups' counts differ by at most
-  // one, and a group that is one short takes its last tile again with every
-  // score at -infinity (launcher: at least one tile each), so all waves run the
-  // same iterations and meet the same barriers.  At the top of iteration i tile
+  // one (launcher: at least one tile each), and a group that is one short loads
+  // and scores its last tile again, so that all waves meet the same barriers, and
+  // leaves it out (a probability of zero would not do: 0 V is a NaN where V is
+  // infinite).  At the top of iteration i tile
   // i's scores are formed and tile i + 1 is waited for; the barrier also frees
   // the stage of tile i - 1 for tile i + 2.
   const int nt = n_kv / BKV, NIT = (nt + KG - 1) / KG;
@@ -325,12 +326,7 @@ __global__ __launch_bounds__(256, D * sizeof(T) >= 384 ? 1 : 2) void attn_genera
     tile(std::true_type{}, i % S, sc, mx, (i + 1) % S, sn);
   };
   auto last = [&](int i, f32x16& sc) __attribute__((always_inline)) {
-    if (!full) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) sc[r] = -INFINITY;
-      mx = -INFINITY;
-    }
-    tile(std::false_type{}, i % S, sc, mx, 0, sc);
+    if (full) tile(std::false_type{}, i % S, sc, mx, 0, sc);
   };
   int i = 0;
   for (; i + 2 < NIT; i += 2) {

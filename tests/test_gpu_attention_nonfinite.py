@@ -45,3 +45,14 @@ def test_infinite_values(orch_lib, dtype, d, split):
     got, ref = _attend(orch_lib, dtype, heads, d, n_q, n_kv, q, K, V, split)
     assert (~np.isfinite(ref)).sum() == 3 * n_q
     _check(got, ref, dtype)
+
+
+@pytest.mark.parametrize("dtype,d,n_kv,key", [("f32", 72, 96, 40),     # two groups, three tiles
+                                              ("bf16", 80, 160, 130),  # four groups, five tiles: in the full group
+                                              ("bf16", 80, 160, 70)])  # and in one that is a tile short
+def test_infinite_value_in_short_group(orch_lib, dtype, d, n_kv, key):
+    heads, n_q, rng = 4, 33, np.random.default_rng(n_kv)
+    q, K, V = (rng.standard_normal((n, heads * d)) * s for n, s in ((n_q, 0.7), (n_kv, 0.7), (n_kv, 1.0)))
+    V[key, 5] = INF
+    got, ref = _attend(orch_lib, dtype, heads, d, n_q, n_kv, q, K, V)
+    _check(got, ref, dtype)
