@@ -34,6 +34,8 @@
 // the key tiles g, g + KG, ..., and the groups' parts of a query meet in LDS at
 // the end.  Splitting the keys inside the workgroup is what fills the chip
 // where the queries alone do not.
+#include <cfloat>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -199,7 +201,9 @@ __global__ __launch_bounds__(256, D * sizeof(T) >= 384 ? 1 : 2) void attn_genera
   for (int t = 0; t < G::DT; ++t)
 #pragma unroll
     for (int r = 0; r < 16; ++r) o[t][r] = 0.0f;
-  float m_run = -INFINITY, l_run = 0.0f;
+  // (the lowest finite number, not -infinity: where every score of a tile is
+  // -infinity, exp2(score - max) is then 0 and not the NaN of inf - inf)
+  float m_run = -FLT_MAX, l_run = 0.0f;
 
   const f32x16 zero16 = {};
   // one K fragment's MFMAs of the score chain
