@@ -204,6 +204,8 @@ __global__ __launch_bounds__(256, D * sizeof(T) >= 384 ? 1 : 2) void attn_genera
   // (the lowest finite number, not -infinity: where every score of a tile is
   // -infinity, exp2(score - max) is then 0 and not the NaN of inf - inf)
   float m_run = -FLT_MAX, l_run = 0.0f;
+  auto is_huge = [](float m) __attribute__((always_inline)) { return fabsf(m) > 0x1p20f && fabsf(m) <= FLT_MAX; };
+  bool huge = true;   // of any query of the wave
 
   const f32x16 zero16 = {};
   // one K fragment's MFMAs of the score chain
@@ -241,11 +243,28 @@ __global__ __launch_bounds__(256, D * sizeof(T) >= 384 ? 1 : 2) void attn_genera
       const float mn = up ? mx : m_run;
       const float alpha = up ? __builtin_amdgcn_exp2f(m_run - mn) : 1.0f;
       m_run = mn;
+      huge = __any(is_huge(mn));
       l_run *= alpha;
 #pragma unroll
       for (int t = 0; t < G::DT; ++t)
 #pragma unroll
         for (int r = 0; r < 16; ++r) o[t][r] *= alpha;
+    }
+    // Past 2^20 the rounding of max = score * scale is no longer small against 1,
+    // and the fused score * scale - max below would show it (scores of the lowest
+    // finite number: an exponent of +-2^102 where 0 is meant).  There the
+    // difference is taken of the rounded product, so that equal scores cancel.
+    float m_sub = m_run;
+    if (__builtin_expect(huge, 0)) {
+#pragma clang fp contract(off)
+      const bool big = is_huge(m_run);
+      const float inv = 1.0f / scale;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const float s = sc[r] * scale;
+        sc[r] = big ? (s - m_run) * inv : sc[r];
+      }
+      m_sub = big ? 0.0f : m_run;
     }
     frag kn[NEXT ? G::NC : 1], v[2][G::DT], hi[2], lo[2];
     if constexpr (NEXT) {
@@ -271,7 +290,7 @@ __global__ __launch_bounds__(256, D * sizeof(T) >= 384 ? 1 : 2) void attn_genera
     };
     auto prob = [&](auto xc, int e) __attribute__((always_inline)) {
       constexpr int x = decltype(xc)::value;
-      pv[e] = __builtin_amdgcn_exp2f(fmaf(sc[EPC * x + e], scale, -m_run));
+      pv[e] = __builtin_amdgcn_exp2f(fmaf(sc[EPC * x + e], scale, -m_sub));
       if (e > 0) take(xc, e - 1);
       if (e == EPC - 1) take(xc, e);
     };

@@ -1,7 +1,7 @@
 """Infinities in K and V of the general attention kernel, against the oracle: an
 infinite value makes its channel infinite (not a NaN) in every query and leaves
-the others alone, and keys whose scores are -infinity take no
-part, also where they fill a key group's first tile.  Tolerances as in the general kernel's tests."""
+the others alone, and keys whose scores are -infinity or the lowest finite number
+take no part, also where they fill a key group's first tile.  Tolerances as in the general kernel's tests."""
 import numpy as np
 import pytest
 import torch
@@ -61,9 +61,13 @@ def test_infinite_value_in_short_group(orch_lib, dtype, d, n_kv, key):
 
 @pytest.mark.parametrize("dtype,d", [("bf16", 64), ("bf16", 80), ("bf16", 128), ("f32", 32), ("f32", 72)])
 @pytest.mark.parametrize("split", [True, False])
-@pytest.mark.parametrize("masked", [(32, 64), (1, 224), (224, 256)])     # key ranges; 32 keys a tile
-def test_masked_keys(orch_lib, dtype, d, split, masked, value=-INF):
-    """Keys masked through a channel of their own (1 in Q): scores of -infinity."""
+@pytest.mark.parametrize("masked", [(32, 64), (1, 224), (224, 256), (0, 256)])     # key ranges; 32 keys a tile
+@pytest.mark.parametrize("value", [-INF, -3.0e38, -1.7e38, -2.9e25])
+def test_masked_keys(orch_lib, dtype, d, split, masked, value):
+    """Keys masked through a channel of their own (1 in Q): scores of -infinity, or
+    the lowest ones (every key masked: all alike)."""
+    if masked == (0, 256) and value == -INF:
+        pytest.skip("no key left")
     heads, n_q, n_kv, rng = 4, 33, 256, np.random.default_rng(d)
     q, K, V = (rng.standard_normal((n, heads * d)) * s for n, s in ((n_q, 0.7), (n_kv, 0.7), (n_kv, 1.0)))
     q[:, ::d], K[:, ::d] = 1.0, 0.0
