@@ -877,29 +877,35 @@ __global__ __launch_bounds__(256) void gemm_bf16_small_kernel(const bf16* __rest
 // fp32 GEMM on v_mfma_f32_32x32x2_f32 (fp32 products and sums; 154 TFLOP/s in a
 // large library product, twice the vector unit without packed instructions).
 // A workgroup is four waves: (BM / 32) x (BN / 32) blocks of 32 x 32 outputs x KG
-// groups that share the k-tiles (group g takes tiles g, g + KG, ...; their sums
-// meet in LDS, added in group order).  k-tiles of 32 (128-byte rows) go straight
+// groups that share the k-tiles.  k-tiles of 32 (128-byte rows) go straight
 // into LDS, a ring of S stages per group, 16-byte chunks XOR-swizzled by row as
 // in the bf16 kernel.  A fragment read gives a lane four consecutive k of its
 // row, one for each of four MFMAs: MFMA e of chunk pair c adds k = 8 c + e and
-// 8 c + 4 + e, the same order in every configuration without key groups.
+// 8 c + 4 + e.
+//
+// Every configuration adds in the same order, that K alone fixes: four sums, of the
+// k-tiles 4 i, 4 i + 1, 4 i + 2 and 4 i + 3, added as ((0 + 1) + 2) + 3.  Group g of KG
+// holds the sums g, g + KG, ... (its k-tiles g, g + KG, ... in turn); the others'
+// meet group 0's in LDS.  So a row's result does not depend on how many rows
+// the call has.
 template <int BM, int BN, int KG, int S>
 struct GemmF32Geo {
   static constexpr int BK = 32, NWG = 4 / KG;             // waves per group
+  static constexpr int SUMS = 4 / KG;                     // sums per group
   static constexpr int WN = BN / 32;
   static constexpr int STAGE = (BM + BN) * BK * 4;
   static constexpr int LPT = (BM + BN) / 8 / NWG;         // 1 KB loads per wave and k-tile
   static constexpr int LDS = KG * S * STAGE;
   static_assert((BM / 32) * (BN / 32) == NWG, "a 32 x 32 block per wave");
   static_assert((BM + BN) / 8 % NWG == 0, "whole loads");
-  static_assert((KG - 1) * NWG * 4096 <= LDS, "the groups' sums fit the ring");
+  static_assert((KG - 1) * NWG * SUMS * 4096 <= LDS, "the groups' sums fit the ring");
 };
 
 template <int BM, int BN, int KG, int S, int EPI>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ W,
                                                        int M, int N, int K, int tiles_n, EpiParams ep) {
   using G = GemmF32Geo<BM, BN, KG, S>;
-  constexpr int LPT = G::LPT;
+  constexpr int LPT = G::LPT, SUMS = G::SUMS;
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   const int lane = threadIdx.x & 63, lr = lane & 31, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -928,21 +934,24 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
   int koff[4];
 #pragma unroll
   for (int c = 0; c < 4; ++c) koff[c] = ((2 * c + h) ^ ((lr >> 1) & 7)) * 16;
-  f32x16 acc;
+  f32x16 acc[SUMS];
 #pragma unroll
-  for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+  for (int u = 0; u < SUMS; ++u)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[u][r] = 0.0f;
 
-  // groups differ by at most one k-tile; all meet every barrier
-  const int KT = K / G::BK, mine = (KT - kg + KG - 1) / KG, NIT = (KT + KG - 1) / KG;
-#pragma unroll
-  for (int t = 0; t < S - 1; ++t)
-    if (t < mine) issue(t, t);
-  for (int t = 0; t < NIT; ++t) {
+  const int KT = K / G::BK, mine = (KT - kg + KG - 1) / KG;   // this group's k-tiles
+  // its t-th k-tile landed and every read of the stage before done, for every wave;
+  // the next load
+  auto turn = [&](int t) __attribute__((always_inline)) {
     if (t + S - 2 < mine) wait_vmcnt<(S - 2) * LPT>();
     else wait_vmcnt<0>();
+    __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
+    __builtin_amdgcn_sched_barrier(0);
     lds_barrier();
     if (t + S - 1 < mine) issue(t + S - 1, (t + S - 1) % S);
-    if (t >= mine) continue;
+  };
+  auto add = [&](int t, f32x16& sum) __attribute__((always_inline)) {
     const char* base = ring + t % S * G::STAGE;
     f32x4 a[4], b[4];
 #pragma unroll
@@ -953,22 +962,50 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
 #pragma unroll
     for (int c = 0; c < 4; ++c)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[c][e], b[c][e], acc, 0, 0, 0);
-  }
-  if constexpr (KG > 1) {
-    lds_barrier();
-    if (kg > 0) {
-      float* part = reinterpret_cast<float*>(smem + ((kg - 1) * G::NWG + wg) * 4096) + lane;
+      for (int e = 0; e < 4; ++e) sum = __builtin_amdgcn_mfma_f32_32x32x2f32(a[c][e], b[c][e], sum, 0, 0, 0);
+  };
 #pragma unroll
-      for (int r = 0; r < 16; ++r) part[r * 64] = acc[r];
+  for (int t = 0; t < S - 1; ++t)
+    if (t < mine) issue(t, t);
+  // four k-tiles a turn, one for each sum; then the last KT % 4, where a group may
+  // be short (all meet every barrier)
+  int t = 0;
+  for (; KG * (t + SUMS) <= KT; t += SUMS) {
+    static_for<0, SUMS>([&](auto uc) {
+      constexpr int u = decltype(uc)::value;
+      turn(t + u);
+      add(t + u, acc[u]);
+    });
+  }
+  static_for<0, SUMS>([&](auto uc) {
+    constexpr int u = decltype(uc)::value;
+    if (KG * (t + u) < KT) {
+      turn(t + u);
+      if (t + u < mine) add(t + u, acc[u]);
+    }
+  });
+  if constexpr (KG > 1) {
+    __syncthreads();
+    if (kg > 0) {
+      float* part = reinterpret_cast<float*>(smem + ((kg - 1) * G::NWG + wg) * SUMS * 4096) + lane;
+#pragma unroll
+      for (int u = 0; u < SUMS; ++u)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) part[(16 * u + r) * 64] = acc[u][r];
     }
     __syncthreads();
     if (kg > 0) return;
+  }
 #pragma unroll
-    for (int g = 0; g < KG - 1; ++g) {
-      const float* part = reinterpret_cast<const float*>(smem + (g * G::NWG + wg) * 4096) + lane;
+  for (int j = 1; j < 4; ++j) {
+    const int g = j % KG, u = j / KG;    // sum j: group g's u-th
+    if (g == 0) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[r] += part[r * 64];
+      for (int r = 0; r < 16; ++r) acc[0][r] += acc[u][r];
+    } else {
+      const float* part = reinterpret_cast<const float*>(smem + ((g - 1) * G::NWG + wg) * SUMS * 4096) + lane;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[0][r] += part[(16 * u + r) * 64];
     }
   }
   // a lane holds column lr, rows 8 g + 4 h .. + 4
@@ -977,7 +1014,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
   const auto col = epi.column(n);
 #pragma unroll
   for (int g = 0; g < 4; ++g) {
-    const float v[4] = {acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]};
+    const float v[4] = {acc[0][4 * g], acc[0][4 * g + 1], acc[0][4 * g + 2], acc[0][4 * g + 3]};
     epi.store4(col, m0 + wg / G::WN * 32 + 8 * g + 4 * h, n, v);
   }
 }
@@ -1281,18 +1318,19 @@ static void launch_f32_tile(const void* A, const void* W, int M, int N, int K, c
                      reinterpret_cast<const float*>(W), M, N, K, tn, ep);
 }
 
-// The split of the four waves.  A 32 x 32 block is one wave's chain of K / 2 MFMAs
-// (64 cycles each), so with few blocks the key groups shorten it, and with some
-// thousands the two-group tile still spreads them more evenly; with more, the 64 x
-// 64 tile loads half the bytes per product.  Measured us for (64, 64, 1) / (32, 64, 2)
-// / (32, 32, 4): 96 x 1536 -> 384 (36 blocks) 40 / 26 / 16; 1000 x 1536 -> 384
-// (384) 43 / 29 / 27; 1000 x 384 -> 1152 (1152) 19.4 / 17.4 / 20.7; 2000 x 3072 -> 768
-// (1512) 125 / 100 / 121; 4096 x 4608 -> 1152 (4608) 446 / 418 / 496; 4096 x 1152 ->
-// 4608 (18432) 398 / 430 / 584.  (The 64 x 64 SIMT tile: 1000 x 384 -> 1152 54 us.)
+// The split of the four waves (the same bits in each).  A 32 x 32 block is one
+// wave's chain of K / 2 MFMAs (64 cycles each), so with few blocks the key groups
+// shorten it, and with some thousands the two-group tile still spreads them more
+// evenly; with more, the 64 x 64 tile loads half the bytes per product.  Measured us
+// for (64, 64, 1) / (32, 64, 2) / (32, 32, 4): 96 x 1536 -> 384 (36 blocks) 35 / 20 /
+// 14; 1000 x 1536 -> 384 (384) 38 / 24 / 25; 1000 x 384 -> 1152 (1152) 18.6 / 15.7 /
+// 18.5; 2000 x 3072 -> 768 (1512) 117 / 95 / 111; 4096 x 4608 -> 1152 (4608) 410 /
+// 390 / 442; 4096 x 1152 -> 4608 (18432) 375 / 401 / 530.  (The 64 x 64 SIMT tile:
+// 1000 x 384 -> 1152 42 us.)
 template <int EPI>
 static void launch_f32(const void* A, const void* W, int M, int N, int K, const EpiParams& ep, hipStream_t s) {
   const long long blocks = (long long)ceil_div(M, 32) * ceil_div(N, 32);
-  if (ep.fixed_order || blocks > 8192) launch_f32_tile<64, 64, 1, 3, EPI>(A, W, M, N, K, ep, s);
+  if (blocks > 8192) launch_f32_tile<64, 64, 1, 3, EPI>(A, W, M, N, K, ep, s);
   else if (blocks > 512) launch_f32_tile<32, 64, 2, 2, EPI>(A, W, M, N, K, ep, s);
   else launch_f32_tile<32, 32, 4, 2, EPI>(A, W, M, N, K, ep, s);
 }

@@ -57,3 +57,21 @@ def test_fixed_order_stitches_fp32(orch_lib):
         ctx.step(x, rb, re, 500, 250, labels, 1.5, kv, 0, out)
         assert torch.equal(out, full[:, 2 * rb:2 * re]), (rb, re)
     ctx.close()
+
+
+@pytest.mark.parametrize("K,N", [(32, 64), (96, 100), (384, 1152), (1184, 384)])     # one, three, twelve, 37 k-tiles
+@pytest.mark.parametrize("epi", [0, 1, 2])
+def test_row_does_not_depend_on_row_count(orch_lib, K, N, epi):
+    """The order of a row's sums is fixed by K: the same bits in calls of one row
+    and of some thousands, whatever tile and key groups they take."""
+    M = 8300 * 1024 // N + 37     # past 8192 blocks of 32 x 32
+    rng = np.random.default_rng(K)
+    A, W, b = to_dev(rng.standard_normal((M, K))), to_dev(rng.standard_normal((N, K)) * 0.02), to_dev(rng.standard_normal(N))
+    gate, h = to_dev(rng.standard_normal((1, N))), to_dev(rng.standard_normal((M, N)))
+    outs = []
+    for m in (1, 33, 500, 600 * 1024 // N, M):
+        out = h[:m].clone() if epi == 2 else empty((m, N))
+        orch_lib.linear(A, m, K, W, N, b, epi, gate if epi == 2 else None, N, m, out, 0)
+        outs.append(out)
+    for out in outs[:-1]:
+        assert torch.equal(out, outs[-1][:out.shape[0]]), out.shape
