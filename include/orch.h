@@ -273,10 +273,10 @@ int orch_set_kernel_timing(orch_ctx* ctx, int enable);
  * output tiles to fill the GPU split K over more waves or workgroups, and
  * attention shares a query tile's keys between waves or workgroups, where
  * that is faster (short bands; over workgroups as the context's workspace
- * allows; the summation order then depends on the band's height).  Off:
- * every GEMM output and every attention query is summed in one chain, so
- * each output's summation order is fixed by the token alone: bands stitched from a buffer holding the full step's K/V
- * reproduce the all-rows step bit for bit.  Takes effect at the next step. */
+ * allows; in bf16 the summation order then depends on the band's height).  Off,
+ * and always in fp32: each output's summation order is fixed by the token
+ * alone: bands stitched from a buffer holding the full step's K/V reproduce
+ * the all-rows step bit for bit.  Takes effect at the next step. */
 int orch_set_work_split(orch_ctx* ctx, int enable);
 int orch_kernel_times(orch_ctx* ctx, double* total_ms, long long* launches);
 

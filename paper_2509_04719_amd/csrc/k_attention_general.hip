@@ -33,7 +33,8 @@
 // A workgroup is four waves, QG query groups x KG key groups: key group g takes
 // the key tiles g, g + KG, ..., and the groups' parts of a query meet in LDS at
 // the end.  Splitting the keys inside the workgroup is what fills the chip
-// where the queries alone do not.
+// where the queries alone do not.  With PARTS = 2 a group walks its keys as two
+// groups would, one after the other: the same bits as twice the groups.
 #include <cfloat>
 
 #include "common.h"
@@ -47,7 +48,7 @@ constexpr float kUp = 1.0f + 0x1p-23f;
 
 constexpr int gcd_(int a, int b) { return b == 0 ? a : gcd_(b, a % b); }
 
-template <typename T, int D, int KG>
+template <typename T, int D, int KG, int PARTS = 1>
 struct Geo {
   static constexpr int EPC = 16 / (int)sizeof(T);     // elements per 16-byte chunk
   static constexpr int KPC = 2 * EPC;                 // contraction depth per fragment pair
@@ -66,8 +67,9 @@ struct Geo {
   static constexpr int PART = (DT * 16 + 2) * 256;    // a wave's O, max and sum
   static constexpr int LDS = KG * S * STAGE;
   static constexpr bool FITS = LDS <= 160 * 1024;
+  static_assert(PARTS == 1 || PARTS == 2, "parts");
   static_assert(D % KPC == 0 && TB % 1024 == 0, "whole fragments and loads");
-  static_assert((KG - 1) * QG * PART <= LDS, "parts fit the ring");
+  static_assert((KG - 1) * PARTS * QG * PART <= LDS, "parts fit the ring");
 };
 
 // Chunk ch of a row of CH chunks lies at position swizzle(ch, row): XOR where
@@ -83,10 +85,10 @@ __device__ __forceinline__ int unswizzle(int pos, int row) {
 __device__ __forceinline__ int kperm(int r) { return (r & ~12) | ((r & 4) << 1) | ((r & 8) >> 1); }
 }  // namespace gen_attn
 
-template <typename T, int D, int KG>
+template <typename T, int D, int KG, int PARTS>
 __global__ __launch_bounds__(256, D * sizeof(T) >= 384 ? 1 : 2) void attn_general_kernel(AttnParams p) {
   using namespace gen_attn;
-  using G = Geo<T, D, KG>;
+  using G = Geo<T, D, KG, PARTS>;
   constexpr bool F32 = sizeof(T) == 4;
   constexpr int QG = G::QG, S = G::S, EPC = G::EPC, ES = (int)sizeof(T);
   constexpr int LPW = (G::NL + QG - 1) / QG;          // loads per wave and tile
@@ -332,7 +334,15 @@ __global__ __launch_bounds__(256, D * sizeof(T) >= 384 ? 1 : 2) void attn_genera
   // the stage of tile i - 1 for tile i + 2.
   const int nt = n_kv / BKV, NIT = (nt + KG - 1) / KG;
   const bool full = kg + KG * (NIT - 1) < nt;
-  auto tile_at = [&](int i) __attribute__((always_inline)) { return kg + KG * (full || i + 1 < NIT ? i : NIT - 2); };
+  // (two parts: the tiles kg, kg + 2 KG, ..., `first` of them, then kg + KG, kg + 3 KG, ...)
+  const int first = (nt - kg + 2 * KG - 1) / (2 * KG);
+  auto tile_at = [&](int i) __attribute__((always_inline)) {
+    const int j = full || i + 1 < NIT ? i : NIT - 2;
+    if constexpr (PARTS == 1) return kg + KG * j;
+    else return kg + (j < first ? 2 * KG * j : KG + 2 * KG * (j - first));
+  };
+  f32x16 o_first[PARTS == 2 ? G::DT : 1];
+  float m_first = 0.0f, l_first = 0.0f;
   f32x16 s0, s1;
   issue(tile_at(0), 0);
   if (1 < NIT) issue(tile_at(1), 1);
@@ -347,6 +357,20 @@ __global__ __launch_bounds__(256, D * sizeof(T) >= 384 ? 1 : 2) void attn_genera
     lds_barrier();
     if (i + 2 < NIT) issue(tile_at(i + 2), (i + 2) % S);
     tile(std::true_type{}, i % S, sc, mx, (i + 1) % S, sn);
+    if constexpr (PARTS == 2) {
+      if (i + 1 == first) {
+        m_first = m_run;
+        l_first = l_run;
+        m_run = -FLT_MAX;
+        l_run = 0.0f;
+        huge = true;
+#pragma unroll
+        for (int t = 0; t < G::DT; ++t) {
+          o_first[t] = o[t];
+          o[t] = zero16;
+        }
+      }
+    }
   };
   auto last = [&](int i, f32x16& sc) __attribute__((always_inline)) {
     if (full) tile(std::false_type{}, i % S, sc, mx, 0, sc);
@@ -364,36 +388,54 @@ __global__ __launch_bounds__(256, D * sizeof(T) >= 384 ? 1 : 2) void attn_genera
   }
 
   l_run += __shfl_xor(l_run, 32, kWave);
+  if constexpr (PARTS == 2) l_first += __shfl_xor(l_first, 32, kWave);
+  // The parts of a query, [register][lane], merged by key group 0 in the order of
+  // their first tiles: part j is group j % KG's, its j / KG-th.
+  f32x16 om[G::DT];
+  float m = PARTS == 2 ? m_first : m_run, l = PARTS == 2 ? l_first : l_run;
+#pragma unroll
+  for (int t = 0; t < G::DT; ++t) om[t] = PARTS == 2 ? o_first[PARTS == 2 ? t : 0] : o[t];
+  auto merge = [&](float m2, float l2, auto&& o2) __attribute__((always_inline)) {
+    const float mn = fmaxf(m, m2);
+    const float f1 = __builtin_amdgcn_exp2f(m - mn), f2 = __builtin_amdgcn_exp2f(m2 - mn);
+    m = mn;
+    l = l * f1 + l2 * f2;
+#pragma unroll
+    for (int t = 0; t < G::DT; ++t)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) om[t][r] = om[t][r] * f1 + o2(t, r) * f2;
+  };
   if constexpr (KG > 1) {
-    // the groups' parts, [register][lane], merged by key group 0 in order
     lds_barrier();
     if (kg > 0) {
-      float* part = reinterpret_cast<float*>(smem + ((kg - 1) * QG + qg) * G::PART) + lane;
+      auto put = [&](int j, float m2, float l2, const f32x16* o2) __attribute__((always_inline)) {
+        float* part = reinterpret_cast<float*>(smem + (((kg - 1) * PARTS + j) * QG + qg) * G::PART) + lane;
 #pragma unroll
-      for (int t = 0; t < G::DT; ++t)
+        for (int t = 0; t < G::DT; ++t)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) part[(16 * t + r) * 64] = o[t][r];
-      part[G::DT * 1024] = m_run;
-      part[G::DT * 1024 + 64] = l_run;
+          for (int r = 0; r < 16; ++r) part[(16 * t + r) * 64] = o2[t][r];
+        part[G::DT * 1024] = m2;
+        part[G::DT * 1024 + 64] = l2;
+      };
+      put(0, m, l, om);
+      if constexpr (PARTS == 2) put(1, m_run, l_run, o);
     }
     __syncthreads();
     if (kg > 0) return;
+  }
 #pragma unroll
-    for (int g = 0; g < KG - 1; ++g) {
-      const float* part = reinterpret_cast<const float*>(smem + (g * QG + qg) * G::PART) + lane;
-      const float m2 = part[G::DT * 1024], mn = fmaxf(m_run, m2);
-      const float f1 = __builtin_amdgcn_exp2f(m_run - mn), f2 = __builtin_amdgcn_exp2f(m2 - mn);
-      m_run = mn;
-      l_run = l_run * f1 + part[G::DT * 1024 + 64] * f2;
-#pragma unroll
-      for (int t = 0; t < G::DT; ++t)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) o[t][r] = o[t][r] * f1 + part[(16 * t + r) * 64] * f2;
+  for (int j = 1; j < KG * PARTS; ++j) {
+    if (j % KG == 0) {
+      merge(m_run, l_run, [&](int t, int r) __attribute__((always_inline)) { return o[t][r]; });
+    } else {
+      const float* part = reinterpret_cast<const float*>(smem + ((j % KG - 1) * PARTS + j / KG) * QG * G::PART + qg * G::PART) + lane;
+      merge(part[G::DT * 1024], part[G::DT * 1024 + 64],
+            [&](int t, int r) __attribute__((always_inline)) { return part[(16 * t + r) * 64]; });
     }
   }
   // a lane holds channels 32 t + 8 g + 4 h .. + 4 of its query
   if (q0 + lc < p.n_q) {
-    const float inv = 1.0f / l_run;
+    const float inv = 1.0f / l;
     T* orow = reinterpret_cast<T*>(p.out) + ((size_t)b * p.n_q + q0 + lc) * H + (size_t)head * D;
     typedef T quad __attribute__((ext_vector_type(4)));
 #pragma unroll
@@ -404,7 +446,7 @@ __global__ __launch_bounds__(256, D * sizeof(T) >= 384 ? 1 : 2) void attn_genera
         if (32 * t + 8 * g + 8 <= D) {
           quad v;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] = from_f<T>(o[t][4 * g + e] * inv);
+          for (int e = 0; e < 4; ++e) v[e] = from_f<T>(om[t][4 * g + e] * inv);
           *reinterpret_cast<quad*>(orow + d) = v;
         }
       }
@@ -425,10 +467,10 @@ bool attention_general_ok(const AttnParams& p, int dtype) {
           p.fresh_n % epc == 0 && p.fresh_off % epc == 0 && (long long)p.fresh_n * p.d < (1ll << 31));
 }
 
-template <typename T, int D, int KG>
+template <typename T, int D, int KG, int PARTS = 1>
 static hipError_t launch_kg(const AttnParams& p, hipStream_t s) {
-  using G = gen_attn::Geo<T, D, KG>;
-  auto kern = attn_general_kernel<T, D, KG>;
+  using G = gen_attn::Geo<T, D, KG, PARTS>;
+  auto kern = attn_general_kernel<T, D, KG, PARTS>;
   static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, G::LDS);
   if (attr != hipSuccess) return attr;
@@ -454,20 +496,30 @@ bool attention_general_better(const AttnParams& p, int dtype) {
 // workgroups of two groups a CU, one of four), 256 waves x 1024 keys 26.3 / 15.7 /
 // 12.2; 512 waves 27.4 / 17.4 / 23.5; 1024 waves 29.8 / 25.7 / 44.9; 2048 waves 44.7 /
 // 47.5 / 87.0; d = 128 (one of two groups), 512 waves 31.7 / 21.7, 1024 waves 35.7 /
-// 42.4; fp32 d = 72 (one of two groups), 512 waves 93 / 53, 1024 waves 96 / 103.
+// 42.4.
+// fp32 takes the same groups whatever the number of queries, so that the order of a
+// query's sums is fixed by its keys: four at d = 32 (or two of two parts each, once
+// four are not resident), else two (one at d = 128, where two do not fit).  d =
+// 72 with 1 / 2 groups: 512 waves 93 / 53, 1024 waves 96 / 103.
 template <typename T, int D, int KG>
 static bool resident(const AttnParams& p) {
   using G = gen_attn::Geo<T, D, KG>;
-  if (!G::FITS || p.fixed_order || p.n_kv / gen_attn::BKV < KG) return false;   // a tile for every group
-  return (long long)ceil_div(p.n_q, 32 * G::QG) * p.heads * p.B <= 256 * (160 * 1024 / G::LDS);
+  return G::FITS && p.n_kv / gen_attn::BKV >= KG &&   // a tile for every group
+         (long long)ceil_div(p.n_q, 32 * G::QG) * p.heads * p.B <= 256 * (160 * 1024 / G::LDS);
 }
 
 template <typename T, int D>
 static hipError_t launch_d(const AttnParams& p, hipStream_t s) {
-  if constexpr (gen_attn::Geo<T, D, 4>::FITS)
-    if (resident<T, D, 4>(p)) return launch_kg<T, D, 4>(p, s);
-  if constexpr (gen_attn::Geo<T, D, 2>::FITS)
-    if (resident<T, D, 2>(p)) return launch_kg<T, D, 2>(p, s);
+  if constexpr (sizeof(T) == 2) {
+    if constexpr (gen_attn::Geo<T, D, 4>::FITS)
+      if (!p.fixed_order && resident<T, D, 4>(p)) return launch_kg<T, D, 4>(p, s);
+    if (!p.fixed_order && resident<T, D, 2>(p)) return launch_kg<T, D, 2>(p, s);
+  } else if constexpr (gen_attn::Geo<T, D, 2>::FITS) {
+    const int nt = p.n_kv / gen_attn::BKV;
+    if constexpr (gen_attn::Geo<T, D, 4>::FITS)
+      if (nt >= 4) return resident<T, D, 4>(p) ? launch_kg<T, D, 4>(p, s) : launch_kg<T, D, 2, 2>(p, s);
+    if (nt >= 2) return launch_kg<T, D, 2>(p, s);
+  }
   return launch_kg<T, D, 1>(p, s);
 }
 

@@ -1,6 +1,6 @@
 """Attention over fresh + stale K/V for the head sizes and types of the
 general matrix-core kernel, against the oracle: every head size, one, two and
-four key groups per workgroup (few, some and many queries), key counts that
+four key groups per workgroup (few, some and many queries; fp32 one or two), key counts that
 leave a key group without a tile, bands that start and end inside a 32-key
 tile, and shapes that keep the scalar kernel (key counts and bands that do not
 allow 16-byte loads).
@@ -9,8 +9,11 @@ Tolerances: fp32 1e-5 as for the scalar kernel.  bf16 2.2e-3: the result is
 rounded once to 8 significant bits (2-norm at most 2^-9 / sqrt(3) x 1.5 =
 1.7e-3 over the mantissa's range); the probabilities keep 16 bits.
 """
+import numpy as np
 import pytest
+import torch
 
+from tests._gpu_util import empty, to_dev
 from tests.test_gpu_kernels import _attention_case
 
 pytestmark = pytest.mark.gpu
@@ -48,3 +51,20 @@ def test_attention_general_running_max(orch_lib, dtype, d, k_ramp, shift):
     tol = 2.2e-3 if dtype == "bf16" else 1.4e-4 if shift else 2e-5
     print(f"  rel-L2 {err:.2e}", flush=True)
     assert err <= tol, err
+
+
+@pytest.mark.parametrize("d", [32, 64, 72, 80, 96, 128])
+@pytest.mark.parametrize("n_kv,fb,nf", [(32, 0, 0), (96, 8, 40), (160, 0, 0), (224, 4, 4), (256, 64, 64)])     # 1, 3, 5, 7, 8 key tiles
+def test_fp32_query_does_not_depend_on_query_count(orch_lib, d, n_kv, fb, nf):
+    """The same bits for a query alone, among few and among thousands."""
+    heads, n_q, rng = 4, 9000, np.random.default_rng(d + n_kv)
+    H = heads * d
+    q, stale, fresh = (to_dev(rng.standard_normal(s) * 0.7) for s in ((heads, n_q, d), (2 * n_kv * H,), (2 * max(nf, 1) * H,)))
+    outs = []
+    for n in (1, 40, 600, n_q):
+        out = empty((n, H))
+        orch_lib.attention(q[:, :n].contiguous(), stale, 2 * n_kv * H, fresh, 2 * max(nf, 1) * H, fb, nf, 1, heads, n,
+                           n_kv, d, out, 0)
+        outs.append(out)
+    for out in outs[:-1]:
+        assert torch.equal(out, outs[-1][:out.shape[0]]), out.shape

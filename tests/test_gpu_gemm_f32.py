@@ -41,15 +41,16 @@ def test_qkv_scatter_f32_ragged(orch_lib, H, heads, n_tok, kv_tokens, off):
     test_qkv_scatter(orch_lib, "f32", H, heads, n_tok, kv_tokens, off)
 
 
-def test_fixed_order_stitches_fp32(orch_lib):
-    """With the work split off, bands of an fp32 model stitch to the all-rows
-    step bit for bit, whatever tiles their heights would choose."""
+@pytest.mark.parametrize("split", [False, True])
+def test_fixed_order_stitches_fp32(orch_lib, split):
+    """Bands of an fp32 model stitch to the all-rows step bit for bit, whatever
+    tiles their heights choose, with the work split off or on."""
     from seeded_inputs import configs, generate
     cfg = configs.scaled(configs.TINY, name="tiny32", latent=32, hidden=256, heads=4, mlp_hidden=1024)
     ctx = orch_lib.DiTStep(cfg, generate.make_weight_blob(cfg, 0))
     x, labels = to_dev(generate.make_latent(cfg, 0)), generate.make_labels(cfg, 0)
     kv = torch.zeros(ctx.stale_kv_bytes() // 4, device=DEV)
-    ctx.set_work_split(False)
+    ctx.set_work_split(split)
     full = empty((4, cfg.latent, cfg.latent))
     ctx.step(x, 0, cfg.R, 500, 250, labels, 1.5, kv, 1, full)
     for rb, re in [(0, 1), (1, 6), (6, 16)]:
