@@ -302,15 +302,16 @@ enum { ORCH_EPI_STORE = 0, ORCH_EPI_GELU = 1, ORCH_EPI_RESIDUAL = 2 };
  * workspace: device memory of at least orch_linear_workspace_bytes() bytes
  * (16-byte aligned) lets a GEMM with too few output tiles to fill the GPU
  * split K over more workgroups (fp32 partials, then a reduction that applies
- * the epilogue); NULL (or fewer bytes) runs without that split (waves of one
- * workgroup may still share K).  The result does not depend on the split
- * beyond rounding. */
+ * the epilogue) or over the waves of a workgroup; NULL runs unsplit: an
+ * output's summation order is then fixed by K alone, not by M.  The result
+ * does not depend on the split beyond rounding. */
 int orch_op_linear(const void* A, int M, int K, const void* W, int N, const float* bias,
                    int epilogue, const float* gate, int gate_stride, int rows_per_batch,
                    void* out, void* workspace, size_t workspace_bytes, int dtype,
                    void* hip_stream);
 
-/* Workspace bytes orch_op_linear can use for this shape (0: never splits). */
+/* Workspace bytes orch_op_linear can use for this shape (0: never splits; 16
+ * where it splits K over waves only, which need the caller's leave, not room). */
 size_t orch_linear_workspace_bytes(int M, int N, int K, int dtype);
 
 /* The QKV projection with its scatter epilogue.  A T [B*n_tok][K], W T

@@ -1109,8 +1109,7 @@ static bool tile_fits(const TileCfg& t, int N, int K) {
 // 210 us in 6 rounds of 256x256 and 284 us in 8 rounds of 256x192 at M = 20480,
 // 131 (4) and 145 us (5) at 12288, 96.6 and 95.0 us (3 each) at 8192; the 128x128
 // tile wins when 256-row tiles would leave most CUs idle.
-static int pick_tile(int M, int N, int K) {
-  const int f = forced_tile();
+static int pick_tile(int M, int N, int K, int f) {
   if (f >= 0 && f < kNumTiles && tile_fits(kTiles[f], N, K)) return f;
   int best = kFallbackTile;
   float best_cost = 0.0f;
@@ -1272,9 +1271,8 @@ static const SmallCfg kSmall[] = {
     {64, 64, 1, 128, true, 0.28f, 0.0f}, {64, 64, 1, 128, false, 0.33f, 0.38f},
 };
 
-static int pick_small(int M, int N, int K, const TileCfg& t, int splits, bool fixed_order) {
+static int pick_small(int M, int N, int K, const TileCfg& t, int splits, bool fixed_order, int f) {
   constexpr int n = sizeof(kSmall) / sizeof(kSmall[0]);
-  const int f = forced_tile();
   if (f >= 0) return f >= kNumTiles && f < kNumTiles + n && K % kSmall[f - kNumTiles].k == 0 ? f - kNumTiles : -1;
   const float kt = K / 64.0f;
   const int rounds = ceil_div(ceil_div(M, t.bm) * (N / t.bn) * splits, 256);
@@ -1340,9 +1338,11 @@ static hipError_t launch_gemm_epi(const void* A, const void* W, int M, int N, in
                                   const EpiParams& ep, int dtype, hipStream_t s) {
   if (M <= 0 || N <= 0 || K <= 0) return hipSuccess;
   if (mfma_path_ok(A, W, N, K, EPI, ep, dtype)) {
-    const int c = pick_tile(M, N, K);
+    const int f = forced_tile(), c = pick_tile(M, N, K, f);
     const int sp = ep.ws && aligned16(ep.ws) ? split_plan(M, N, K, kTiles[c], ep.ws_elems) : 1;
-    const int sm = pick_small(M, N, K, kTiles[c], sp, ep.fixed_order);
+    // a workspace smaller than the plan's is no leave to share K
+    const bool fixed = ep.fixed_order || (ep.ws && sp < split_plan(M, N, K, kTiles[c], (size_t)-1));
+    const int sm = pick_small(M, N, K, kTiles[c], sp, fixed, f);
     if (sm >= 0) {
       launch_small<EPI>(sm, A, W, M, N, K, ep, s);
     } else if (sp > 1) {
@@ -1370,10 +1370,13 @@ static hipError_t launch_gemm_epi(const void* A, const void* W, int M, int N, in
 
 size_t gemm_split_workspace_elems(int M, int N, int K, int dtype) {
   if (M <= 0 || !gemm_uses_mfma(N, K, dtype)) return 0;
-  const int c = pick_tile(M, N, K);
+  const int f = forced_tile(), c = pick_tile(M, N, K, f);
   if (!tile_fits(kTiles[c], N, K)) return 0;
   const int sp = split_plan(M, N, K, kTiles[c], (size_t)-1);
-  return sp > 1 ? (size_t)sp * M * N : 0;
+  if (sp > 1) return (size_t)sp * M * N;
+  // waves that share K need no room, but a caller's leave: 16 bytes
+  const int sm = pick_small(M, N, K, kTiles[c], 1, false, f);
+  return sm >= 0 && kSmall[sm].groups > 1 ? 4 : 0;
 }
 
 hipError_t launch_gemm(const void* A, const void* W, int M, int N, int K, int epi,

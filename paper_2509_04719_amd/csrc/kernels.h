@@ -36,7 +36,8 @@ struct EpiParams {
   bool fixed_order = false;
 };
 
-// Workspace elements (fp32) the GEMM's k-split takes for this shape (0: no split).
+// Workspace elements (fp32) the GEMM's k-split takes for this shape (0: no split;
+// 4, where only waves of a workgroup share K: the caller's leave to do so).
 size_t gemm_split_workspace_elems(int M, int N, int K, int dtype);
 
 // y = A W^T (+ epilogue).  A T [M][K], W T [N][K].

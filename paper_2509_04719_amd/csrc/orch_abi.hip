@@ -865,6 +865,7 @@ int orch_op_linear(const void* A, int M, int K, const void* W, int N, const floa
     ep.ws = (float*)workspace;
     ep.ws_elems = workspace_bytes / sizeof(float);
   }
+  ep.fixed_order = ep.ws_elems < 4;   // no workspace, no leave to share K
   HIP_TRY(launch_gemm(A, W, M, N, K, epilogue, ep, dtype, (hipStream_t)hip_stream), "linear launch");
   return ORCH_OK;
 }
@@ -883,6 +884,7 @@ int orch_op_qkv_projection(const void* A, int B, int n_tok, int K, const void* W
   ep.bias = bias; ep.rows_per_batch = n_tok < 1 ? 1 : n_tok; ep.q = q_out; ep.kv = kv_out;
   ep.kv_branch_stride = kv_branch_stride; ep.kv_tokens = kv_tokens; ep.tok_offset = tok_offset;
   ep.heads = heads; ep.hidden = hidden; ep.head_dim = hidden / heads;
+  ep.fixed_order = true;
   HIP_TRY(launch_gemm(A, W, B * n_tok, 3 * hidden, K, kEpiQkv, ep, dtype, (hipStream_t)hip_stream),
           "qkv launch");
   return ORCH_OK;
