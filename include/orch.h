@@ -332,15 +332,18 @@ int orch_op_qkv_projection(const void* A, int B, int n_tok, int K, const void* W
  * fresh_branch_stride) and from `kv_stale` otherwise (buffer layout, branch
  * stride stale_branch_stride).  n_fresh may be 0.  out T [B][n_q][H].
  * workspace: device memory of at least orch_attention_workspace_bytes() bytes
- * lets short bands split the keys over more workgroups; NULL (or fewer
- * bytes) runs without that split (waves of one workgroup may still share the
- * keys).  The result does not depend on the split beyond rounding. */
+ * lets short bands split the keys over more workgroups, or over the waves of a
+ * workgroup; NULL (or fewer bytes) runs unsplit: a query's summation order is
+ * then fixed by its keys alone, not by n_q.  The result does not depend on the
+ * split beyond rounding. */
 int orch_op_attention(const void* q, const void* kv_stale, size_t stale_branch_stride,
                       const void* kv_fresh, size_t fresh_branch_stride, int fresh_begin,
                       int n_fresh, int B, int heads, int n_q, int n_kv, int head_dim, void* out,
                       void* workspace, size_t workspace_bytes, int dtype, void* hip_stream);
 
-/* Workspace bytes orch_op_attention can use for this shape (0: never splits). */
+/* Workspace bytes orch_op_attention can use for this shape (0: never splits; 16
+ * where it splits the keys over waves only, which need the caller's leave, not
+ * room). */
 size_t orch_attention_workspace_bytes(int B, int heads, int n_q, int n_kv, int head_dim,
                                       int dtype);
 

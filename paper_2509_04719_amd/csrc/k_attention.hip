@@ -797,8 +797,10 @@ static AttnPlan plan_attention(int B, int heads, int n_q, int n_kv, int d) {
 }
 
 size_t attention_workspace_bytes(int B, int heads, int n_q, int n_kv, int d, int dtype) {
-  if (n_q <= 0 || B <= 0 || heads <= 0 || !attention_uses_mfma(d, n_kv, dtype)) return 0;
-  return plan_attention(B, heads, n_q, n_kv, d).ws_bytes;
+  if (n_q <= 0 || B <= 0 || heads <= 0) return 0;
+  const size_t plan = attention_uses_mfma(d, n_kv, dtype) ? plan_attention(B, heads, n_q, n_kv, d).ws_bytes : 0;
+  // waves that share keys need no room, but a caller's leave: 16 bytes
+  return plan == 0 && attention_general_shares(B, heads, n_q, n_kv, d, dtype) ? 16 : plan;
 }
 
 static bool aligned16(const void* ptr) { return ((uintptr_t)ptr & 15) == 0; }

@@ -523,6 +523,21 @@ static hipError_t launch_d(const AttnParams& p, hipStream_t s) {
   return launch_kg<T, D, 1>(p, s);
 }
 
+// Whether waves share a query's keys at this shape, if the call leaves them free to.
+bool attention_general_shares(int B, int heads, int n_q, int n_kv, int d, int dtype) {
+  AttnParams p{};
+  p.B = B; p.heads = heads; p.n_q = n_q; p.n_kv = n_kv; p.d = d;
+  if (dtype != kBF16 || !attention_general_ok(p, dtype)) return false;
+  switch (d) {
+    case 32: return resident<bf16, 32, 2>(p);
+    case 64: return attention_general_better(p, dtype) || (!attention_uses_mfma(d, n_kv, dtype) && resident<bf16, 64, 2>(p));
+    case 80: return resident<bf16, 80, 2>(p);
+    case 96: return resident<bf16, 96, 2>(p);
+    case 128: return resident<bf16, 128, 2>(p);
+  }
+  return false;
+}
+
 hipError_t launch_attention_general(const AttnParams& p, int dtype, hipStream_t s) {
   if (dtype == kBF16) {
     switch (p.d) {

@@ -86,7 +86,8 @@ struct AttnParams {
 };
 
 // Workspace bytes that let the attention cut query tiles between workgroups
-// for this shape (0: tiles stay whole).
+// for this shape (0: tiles stay whole; 16, where only waves of a workgroup share
+// keys: the caller's leave to do so).
 size_t attention_workspace_bytes(int B, int heads, int n_q, int n_kv, int d, int dtype);
 hipError_t launch_attention(const AttnParams& p, int dtype, hipStream_t stream);
 bool attention_uses_mfma(int d, int n_kv, int dtype);
@@ -95,6 +96,7 @@ bool attention_uses_mfma(int d, int n_kv, int dtype);
 // beats the 64-channel instance of the other kernel.
 bool attention_general_ok(const AttnParams& p, int dtype);
 bool attention_general_better(const AttnParams& p, int dtype);
+bool attention_general_shares(int B, int heads, int n_q, int n_kv, int d, int dtype);
 hipError_t launch_attention_general(const AttnParams& p, int dtype, hipStream_t stream);
 
 // Conditioning.  temb: fp32 [H] scratch; sc: fp32 [B][H] SiLU(c);

@@ -945,6 +945,8 @@ int orch_op_attention(const void* q, const void* kv_stale, size_t stale_bs, cons
   AttnParams ap = orch_detail::attention_params(q, kv_stale, stale_bs, kv_fresh, fresh_bs, fresh_begin,
                                    n_fresh, B, heads, n_q, n_kv, head_dim, out);
   ap.ws = workspace; ap.ws_bytes = workspace ? workspace_bytes : 0;
+  // less workspace than asked for is no leave to share a query's keys
+  ap.fixed_order = ap.ws_bytes == 0 || ap.ws_bytes < attention_workspace_bytes(B, heads, n_q, n_kv, head_dim, dtype);
   HIP_TRY(launch_attention(ap, dtype, (hipStream_t)hip_stream), "attention launch");
   return ORCH_OK;
 }

@@ -58,3 +58,38 @@ def test_linear_workspace_is_the_leave(orch_lib, M, N, K):
     assert torch.equal(outs[0], outs[1])
     # two roundings to bf16 of the same sums
     assert float((outs[0] - outs[2]).norm() / outs[0].norm()) <= 2 * 2.0 ** -9
+
+
+@pytest.mark.parametrize("d", [32, 64, 72, 80, 96, 128])
+@pytest.mark.parametrize("n_kv,fb,nf", [(64, 0, 0), (576, 64, 64), (1024, 0, 0)])
+def test_attention_query(orch_lib, d, n_kv, fb, nf):
+    """Few queries (where waves would share their keys) to many."""
+    heads, n_q, rng = 6, 3000, np.random.default_rng(d + n_kv)
+    H = heads * d
+    q, stale, fresh = (to_dev(rng.standard_normal(s) * 0.7, "bf16")
+                       for s in ((heads, n_q, d), (2 * n_kv * H,), (2 * max(nf, 1) * H,)))
+    outs = []
+    for n in (1, 96, 700, n_q):
+        out = empty((n, H), "bf16")
+        orch_lib.attention(q[:, :n].contiguous(), stale, 2 * n_kv * H, fresh, 2 * max(nf, 1) * H, fb, nf, 1, heads, n,
+                           n_kv, d, out, 1)
+        outs.append(out)
+    for out in outs[:-1]:
+        assert torch.equal(out, outs[-1][:out.shape[0]]), out.shape
+
+
+@pytest.mark.parametrize("d", [32, 64, 80, 128])
+def test_attention_workspace_is_the_leave(orch_lib, d):
+    heads, n_q, n_kv, rng = 6, 96, 256, np.random.default_rng(d)
+    H, need = heads * d, orch_lib.attention_workspace_bytes(1, heads, n_q, n_kv, d, 1)
+    assert need > 0
+    q, stale = (to_dev(rng.standard_normal(s) * 0.7, "bf16") for s in ((heads, n_q, d), (2 * n_kv * H,)))
+    outs = []
+    for bytes_ in (0, 8, need):
+        out = empty((n_q, H), "bf16")
+        w = torch.empty(bytes_, dtype=torch.uint8, device=q.device) if bytes_ else None
+        orch_lib.attention(q, stale, 2 * n_kv * H, None, 0, 0, 0, 1, heads, n_q, n_kv, d, out, 1, workspace=w)
+        outs.append(out.float())
+    assert torch.equal(outs[0], outs[1])
+    # 1e-2 as between the attention kernels and the oracle
+    assert float((outs[0] - outs[2]).norm() / outs[0].norm()) <= 1e-2
