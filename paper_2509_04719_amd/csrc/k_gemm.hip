@@ -1250,11 +1250,14 @@ static void launch_small_tile(const void* A, const void* W, int M, int N, int K,
 // Whether and how to use the small kernel: the configuration with the least
 // estimated time, if that is below the estimate of the tile and k-split chosen
 // otherwise.  Estimates in us over the k-tiles of 64, fitted to M from 32 to 3328
-// at the DiT projections of hidden 384, 768 and 1152:
-//   small  2.5 + KT max(b, c WGs / 256): b a lone workgroup's k-tile, c what a CU
+// at the DiT projections of hidden 384, 768 and 1152 and checked from 8 rows and K =
+// 64 on:
+//   small  2.5 + max(KT' b, KT c WGs / 256): KT' the k-tiles rounded up to whole turns
+//          of the groups, b a lone workgroup's k-tile (a group's turn, shared by the
+//          groups), c what a CU
 //          needs per workgroup's k-tile when several share it (about 54 B per
 //          ns and CU of operands from L2, the same for all of them); one
-//          workgroup per CU (LDS): 2.5 + KT b rounds + 1.5 per further round
+//          workgroup per CU (LDS): 2.5 + KT' b rounds + 1.5 per further round
 //   128^2  4.5 + 0.42 KT / splits a round, plus 5 and 8 B of partials per split
 //          and output at 6 TB/s with a k-split
 // Measured, us before -> after: hidden 384, M = 96: qkv 5.3 -> 3.6, out-proj 6.5 -> 3.7,
@@ -1274,7 +1277,7 @@ static const SmallCfg kSmall[] = {
 static int pick_small(int M, int N, int K, const TileCfg& t, int splits, bool fixed_order, int f) {
   constexpr int n = sizeof(kSmall) / sizeof(kSmall[0]);
   if (f >= 0) return f >= kNumTiles && f < kNumTiles + n && K % kSmall[f - kNumTiles].k == 0 ? f - kNumTiles : -1;
-  const float kt = K / 64.0f;
+  const int kt = K / 64;
   const int rounds = ceil_div(ceil_div(M, t.bm) * (N / t.bn) * splits, 256);
   if (t.bm != 128 || rounds > 1) return -1;
   float best = 4.5f + 0.42f * kt / splits + (splits > 1 ? 5.0f + splits * ((float)M * N * 8e-6f / 6.0f) : 0.0f);
@@ -1283,8 +1286,8 @@ static int pick_small(int M, int N, int K, const TileCfg& t, int splits, bool fi
     const SmallCfg& c = kSmall[i];
     if (K % c.k || (fixed_order && c.groups > 1)) continue;
     const int wgs = ceil_div(M, c.bm) * (N / c.bn), r = ceil_div(wgs, 256);
-    const float per = c.c * wgs / 256.0f;
-    const float us = c.one ? 2.5f + kt * c.b * r + 1.5f * (r - 1) : 2.5f + kt * (per > c.b ? per : c.b);
+    const float alone = ceil_div(kt, c.groups) * c.groups * c.b, shared = kt * c.c * wgs / 256.0f;
+    const float us = 2.5f + (c.one ? alone * r + 1.5f * (r - 1) : alone > shared ? alone : shared);
     if (us < best) {
       best = us;
       pick = i;
