@@ -178,20 +178,20 @@ struct StripEpilogue {
     f32x4 h[PRE_H ? RIT : 1], g[PRE_H ? RIT : 1], rb[PRE_H ? RIT : 1];
   };
 
-  // bias: that of column n0 (global memory or LDS)
-  __device__ __forceinline__ void prefetch(Pre& pre, int lane, int m0, int n0, const float* bias) const {
+  // bias[nb]: that of column n0 (global memory, or the tile's in LDS)
+  __device__ __forceinline__ void prefetch(Pre& pre, int lane, int m0, int n0, const float* bias, int nb) const {
     if constexpr (BIAS8) {
       constexpr int CH = TN / 8;
 #pragma unroll
       for (int q = 0; q < NB; ++q) {
-        const int n = ((q * 64 + lane) % CH) * 8;
+        const int n = nb + ((q * 64 + lane) % CH) * 8;
         pre.b[q][0] = *reinterpret_cast<const f32x4*>(bias + n);
         pre.b[q][1] = *reinterpret_cast<const f32x4*>(bias + n + 4);
       }
     }
     if constexpr (EPI == kEpiQkv) {
 #pragma unroll
-      for (int q = 0; q < TN / 16; ++q) pre.vb[q] = bias[q * 16 + (lane >> 2)];
+      for (int q = 0; q < TN / 16; ++q) pre.vb[q] = bias[nb + q * 16 + (lane >> 2)];
     }
     if constexpr (PRE_H) {
       constexpr int CH = TN / 4;
@@ -551,7 +551,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_kernel(const bf16* __r
   using E = StripEpilogue<FM, FN, EPI>;
   const E epi{ep, M, N, split};
   typename E::Pre pre;
-  epi.prefetch(pre, lane, m0 + wm * G::TM, n0 + wn * G::TN, ep.bias + n0 + wn * G::TN);
+  epi.prefetch(pre, lane, m0 + wm * G::TM, n0 + wn * G::TN, ep.bias, n0 + wn * G::TN);
 
 #pragma unroll
   for (int s = 0; s < S - 1; ++s) static_for<0, LPT>([&](auto jc) { dma(jc, s, s); });
@@ -749,7 +749,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_phased_kernel(const bf16* __res
 
   static_assert(8 * E::BYTES <= 8 * HALF, "epilogue staging fits the stages");
   lds_barrier();
-  epi.prefetch(pre, lane, m0 + wm * 128, n0 + wn * 64, reinterpret_cast<const float*>(smem + 8 * HALF) + wn * 64);
+  epi.prefetch(pre, lane, m0 + wm * 128, n0 + wn * 64, reinterpret_cast<const float*>(smem + 8 * HALF), wn * 64);
   epi.run(acc, reinterpret_cast<float*>(smem + wave * E::BYTES), lane, m0 + wm * 128, n0 + wn * 64, pre);
 #endif
 }
@@ -792,7 +792,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_small_kernel(const bf16* __rest
   using E = StripEpilogue<1, 1, EPI>;
   const E epi{ep, M, N, 0};
   typename E::Pre pre;
-  if (kg == 0) epi.prefetch(pre, lane, mw, nw, ep.bias + nw);
+  if (kg == 0) epi.prefetch(pre, lane, mw, nw, ep.bias, nw);
 
   // load i of a k-tile: rows 8 (wg LPT + i) .. + 8 (A first, then W); A rows past
   // M re-read row M - 1
