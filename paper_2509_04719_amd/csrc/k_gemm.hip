@@ -609,8 +609,7 @@ constexpr int at(int x, int st) { return ((x & 2) * 2 + st * 2 + (x & 1)) * HALF
 
 template <int EPI>
 __global__ __launch_bounds__(512) void gemm_bf16_phased_kernel(const bf16* __restrict__ A, const bf16* __restrict__ W,
-                                                               int M, int N, int K, int ldk, int tiles_m, int tiles_n,
-                                                               EpiParams ep) {
+                                                               int M, int N, int K, int tiles_m, int tiles_n, EpiParams ep) {
   // (device-only types: the host pass needs the launch stub alone)
 #if defined(__HIP_DEVICE_COMPILE__)
   using namespace ph;
@@ -632,14 +631,14 @@ __global__ __launch_bounds__(512) void gemm_bf16_phased_kernel(const bf16* __res
     const unsigned ch = (unsigned)((lane & 7) ^ ((r >> 1) & 7)) * 16u;
 #pragma unroll
     for (int x = 0; x < 2; ++x) {
-      off[kA0 + x][q] = (unsigned)min(m0 + 128 * (r >> 6) + 64 * x + (r & 63), M - 1) * (unsigned)ldk * 2u + ch;
-      off[kW0 + x][q] = (unsigned)(n0 + 64 * (r >> 5) + 32 * x + (r & 31)) * (unsigned)ldk * 2u + ch;
+      off[kA0 + x][q] = (unsigned)min(m0 + 128 * (r >> 6) + 64 * x + (r & 63), M - 1) * (unsigned)K * 2u + ch;
+      off[kW0 + x][q] = (unsigned)(n0 + 64 * (r >> 5) + 32 * x + (r & 31)) * (unsigned)K * 2u + ch;
     }
   }
   // (buffer loads: the k-tile is a scalar offset, the lane's offset constant; the
   // launcher keeps both matrices under 2 GiB)
-  const __amdgpu_buffer_rsrc_t rA = buffer_rsrc(A + (size_t)ta.split * K, ((size_t)(M - 1) * ldk + K) * 2);
-  const __amdgpu_buffer_rsrc_t rW = buffer_rsrc(W + (size_t)ta.split * K, ((size_t)(N - 1) * ldk + K) * 2);
+  const __amdgpu_buffer_rsrc_t rA = buffer_rsrc(A, (size_t)M * K * 2);
+  const __amdgpu_buffer_rsrc_t rW = buffer_rsrc(W, (size_t)N * K * 2);
   // load q of half x of k-tile kt into stage st
   auto load = [&](int x, int q, int st, int kt) __attribute__((always_inline)) {
     __builtin_amdgcn_raw_ptr_buffer_load_lds(x < kW0 ? rA : rW,
@@ -692,7 +691,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_phased_kernel(const bf16* __res
     });
   };
   using E = StripEpilogue<4, 2, EPI>;
-  const E epi{ep, M, N, ta.split};
+  const E epi{ep, M, N, 0};
   typename E::Pre pre;
   using I0 = std::integral_constant<int, 0>;
   using I1 = std::integral_constant<int, 1>;
@@ -1103,12 +1102,14 @@ static bool tile_fits(const TileCfg& t, int N, int K) {
 // Pick the configuration with the least estimated time: whole rounds of tiles
 // over the 256 CUs times the tile area, divided by the tile's relative
 // throughput per CU.  The throughputs were measured on the DiT-XL projection
-// shapes (K = 1152 and 4608, M from 768 to 20480).  A round costs about 8 us
-// (first loads, epilogue) plus 1.55 us per 64-deep k-tile with 256x256 tiles,
-// 1.33 us with 256x192, and 6 us plus 0.49 us with 128x128: 1152 -> 4608 takes
-// 210 us in 6 rounds of 256x256 and 284 us in 8 rounds of 256x192 at M = 20480,
-// 131 (4) and 145 us (5) at 12288, 96.6 and 95.0 us (3 each) at 8192; the 128x128
-// tile wins when 256-row tiles would leave most CUs idle.
+// shapes (K = 1152 and 4608, M from 768 to 20480).  A round of K = 1152 takes 31 to
+// 35 us with 256x256 tiles, 27 to 29 with 256x192 and 12 with 128x128: 1152 -> 4608
+// takes 195 us in 6 rounds of 256x256 and 231 us in 8 rounds of 256x192 at M = 20480,
+// 121 (4) and 136 us (5) at 12288, 86 and 88 us (3 each) at 8192; the 128x128
+// tile wins when 256-row tiles would leave most CUs idle.  The rating of 256x256
+// holds for both of its loops: where only the plain one runs (K an odd multiple of
+// 64), 256x256 against 256x192 is 20.8 / 24.7 us at 16896 x 192 -> 1536, 52.2 / 56.4 at
+// 12288 x 320 -> 4608, 201 / 220 at 20480 x 1088 -> 4608.
 static int pick_tile(int M, int N, int K, int f) {
   if (f >= 0 && f < kNumTiles && tile_fits(kTiles[f], N, K)) return f;
   int best = kFallbackTile;
@@ -1200,8 +1201,7 @@ static int split_plan(int M, int N, int K, const TileCfg& t, size_t ws_elems) {
 }
 
 template <int EPI>
-static void launch_phased(const void* A, const void* W, int M, int N, int K, const EpiParams& ep0, hipStream_t s,
-                          int splits) {
+static void launch_phased(const void* A, const void* W, int M, int N, int K, const EpiParams& ep0, hipStream_t s) {
   EpiParams ep = ep0;
   if (EPI == kEpiQkv) ep.hd_magic = (unsigned)((0x100000000ull + ep.head_dim - 1) / ep.head_dim);
   auto kern = gemm_bf16_phased_kernel<EPI>;
@@ -1209,8 +1209,8 @@ static void launch_phased(const void* A, const void* W, int M, int N, int K, con
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, ph::LDS);
   (void)attr;
   const int tm = ceil_div(M, ph::BM), tn = N / ph::BN;
-  hipLaunchKernelGGL(kern, dim3(tm * tn * splits), dim3(512), ph::LDS, s, reinterpret_cast<const bf16*>(A),
-                     reinterpret_cast<const bf16*>(W), M, N, K / splits, K, tm, tn, ep);
+  hipLaunchKernelGGL(kern, dim3(tm * tn), dim3(512), ph::LDS, s, reinterpret_cast<const bf16*>(A),
+                     reinterpret_cast<const bf16*>(W), M, N, K, tm, tn, ep);
 }
 
 template <int EPI>
@@ -1221,12 +1221,15 @@ static void launch_tile_cfg(int c, const void* A, const void* W, int M, int N, i
       // More than one round: the phased kernel (1152 -> 4608, M = 20480: 229 -> 210
       // us).  In a single round the plain loop: there the phased kernel is 2 us
       // faster by itself (M = 3328 in a step: 38.4 -> 36.5 us), but the
-      // attention after it loses as much (71.9 -> 73.5 us) and the step 1%.
-      if (K / splits % 128 == 0 && ceil_div(M, ph::BM) * (N / ph::BN) * splits > 256 &&
-          (size_t)cmax(M, N) * K < (size_t)1 << 30)
-        launch_phased<EPI>(A, W, M, N, K, ep, s, splits);
-      else
-        launch_tile<256, 256, 64, 2, 4, 2, EPI>(A, W, M, N, K, ep, s, splits);
+      // attention after it loses as much (71.9 -> 73.5 us) and the step 1%.  (A
+      // k-split is one round at most: split_plan.)
+      if constexpr (EPI != kEpiPartial) {
+        if (K % 128 == 0 && ceil_div(M, ph::BM) * (N / ph::BN) > 256 && (size_t)cmax(M, N) * K < (size_t)1 << 30) {
+          launch_phased<EPI>(A, W, M, N, K, ep, s);
+          break;
+        }
+      }
+      launch_tile<256, 256, 64, 2, 4, 2, EPI>(A, W, M, N, K, ep, s, splits);
       break;
     case 1: launch_tile<256, 192, 64, 4, 2, 2, EPI>(A, W, M, N, K, ep, s, splits); break;
     case 2: launch_tile<128, 128, 64, 4, 2, 4, EPI>(A, W, M, N, K, ep, s, splits); break;
