@@ -529,16 +529,16 @@ __global__ __launch_bounds__(256) void conv_split_reduce_kernel(UNetConvParams p
 // The launch plan: a tile shape (each that divides C_out) and a split of
 // the 9 C / 64 k-tiles (tap, channel chunk) into 1, 2, 3, 4, 6, 9 or 16
 // even ranges over more workgroups (at least four k-tiles each), whichever
-// has the least estimated time.  The estimate, fitted by least squares (with
-// non-negative terms) to every shape and split count on twelve bands of the
-// three SDXL-sized stages on MI355X: each round of workgroups over the slots
+// has the least estimated time.  The estimate, fitted to every shape and split count
+// on 27 bands (twelve of the three SDXL-sized stages, 15 of other maps, 16 to 128
+// pixels wide, 64 to 1280 channels) on MI355X: each round of workgroups over the slots
 // (256 CUs x workgroups per CU) costs its K k-tiles x (a + b x the round's
-// fill), a and b per shape (narrow 0.30 + 0.31 fill us, wide 0.42 + 0.12,
-// mid 0.51: a lone workgroup's k-tile, and what the round's sharing of CUs
+// fill), a and b per shape (narrow 0.25 + 0.28 fill us, wide 0.33 + 0.11,
+// mid 0.43: a lone workgroup's k-tile, and what the round's sharing of CUs
 // and bandwidth adds); a split adds the fp32 partials' round trip (written
-// by the convolution, added in order by the reduction kernel) at 0.43 us
-// per MB.  On those bands it picks plans within 3 us each of the fastest
-// measured since.
+// by the convolution, added in order by the reduction kernel) at 0.44 us
+// per MB.  It picks the fastest plan measured on 24 of the bands and loses 0.1, 0.4 and
+// 1.9 us of 23, 35 and 29 on the others.
 struct ConvPlan {
   int geo;     // 0: narrow, 1: wide, 2: mid
   int splits;
@@ -554,7 +554,7 @@ static ConvPlan conv_best_splits(int geo, double a, double b, int M, int C, int 
   for (const int s : {1, 2, 3, 4, 6, 9, 16}) {
     if (s > 1 && kts < 4 * s) break;
     const int wgs = tiles * s, rounds = ceil_div(wgs, slots);
-    const double us = ceil_div(kts, s) * (rounds * a + b * wgs / slots) + (s > 1 ? 0.43 * s * mb : 0.0);
+    const double us = ceil_div(kts, s) * (rounds * a + b * wgs / slots) + (s > 1 ? 0.44 * s * mb : 0.0);
     if (s == 1 || us < *best_us) {
       best.splits = s;
       *best_us = us;
@@ -567,13 +567,13 @@ static ConvPlan conv_best_splits(int geo, double a, double b, int M, int C, int 
 static ConvPlan conv_plan(int M, int C, int C_out) {
   double us = 0.0, u = 0.0;
   ConvPlan best{-1, 0};
-  if (C_out % conv::Wide::BN == 0) best = conv_best_splits<conv::Wide>(1, 0.42, 0.12, M, C, C_out, &us);
+  if (C_out % conv::Wide::BN == 0) best = conv_best_splits<conv::Wide>(1, 0.33, 0.11, M, C, C_out, &us);
   {
-    const ConvPlan n = conv_best_splits<conv::Narrow>(0, 0.30, 0.31, M, C, C_out, &u);
+    const ConvPlan n = conv_best_splits<conv::Narrow>(0, 0.25, 0.28, M, C, C_out, &u);
     if (best.geo < 0 || u < us) { best = n; us = u; }
   }
   if (C_out % conv::Mid::BN == 0) {
-    const ConvPlan m = conv_best_splits<conv::Mid>(2, 0.51, 0.0, M, C, C_out, &u);
+    const ConvPlan m = conv_best_splits<conv::Mid>(2, 0.43, 0.0, M, C, C_out, &u);
     if (u < us) best = m;
   }
   return best;

@@ -177,8 +177,8 @@ UNET_SDXL_1024_S3 = UNetConvConfig(name="unet_sdxl_1024_stage3", height=32, widt
 
 # A map of 120 x 120 pixels (14400 in all rows, 3120 in a 26-row band: both
 # end in a partial 128-pixel tile), 192 -> 320 channels: the convolution takes
-# 160-channel tiles for all rows (one round of workgroups) and for the 26-row
-# band (its 27 k-tiles split three ways).
+# 160-channel tiles for all rows (one round of workgroups) and 64-channel tiles
+# for the 26-row band.
 UNET_RAGGED_320 = UNetConvConfig(name="unet_ragged_320", height=120, width=120, channels=192, groups=8,
                                  out_channels=320, band_rows=(120, 26), share_labels=("all rows", "26 rows"))
 

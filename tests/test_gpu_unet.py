@@ -105,9 +105,8 @@ def test_unet_sdxl_deeper_stages(orch_lib, name, rows, share):
 
 
 # 120 x 120 x 192 -> 320: every row (the whole map in 160-channel tiles, the
-# last pixel tile partial), an interior band (64-channel tiles) and a 26-row
-# band (160-channel tiles, k-tiles split three ways, the last pixel tile
-# partial)
+# last pixel tile partial), an interior band and a 26-row band (64-channel
+# tiles; the last pixel tile of the 26 rows partial)
 @pytest.mark.parametrize("rb,re,refresh", [(0, 120, 1), (30, 90, 0), (40, 66, 1)],
                          ids=["all", "interior", "26 rows"])
 def test_unet_ragged_320_channels(orch_lib, rb, re, refresh):
