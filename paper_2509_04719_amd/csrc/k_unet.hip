@@ -272,14 +272,14 @@ __global__ __launch_bounds__(256) void gn_silu_kernel(UNetConvParams p) {
 // more workgroups; the fp32 partial sums are added in order by a second
 // kernel, which adds the bias.
 namespace conv {
-constexpr int BK = 64;
+constexpr int BM = 128, BK = 64;
 constexpr int ROWB = 2 * BK;                         // bytes per LDS row
 // BM pixels x BN output channels per workgroup on WM x WN waves (wave tile TM
 // pixels x TN channels), MF x MF MFMA blocks (32: v_mfma_f32_32x32x16_bf16, 16:
 // v_mfma_f32_16x16x32_bf16), a ring of S stages
-template <int BM_, int BN_, int WM_, int WN_, int S_, int MF_>
+template <int BN_, int WM_, int WN_, int S_, int MF_>
 struct Geo {
-  static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, NW = WM_ * WN_, S = S_, MF = MF_;
+  static constexpr int BN = BN_, WM = WM_, WN = WN_, NW = WM_ * WN_, S = S_, MF = MF_;
   static constexpr int TM = BM / WM, TN = BN / WN;
   static constexpr int FM = TM / MF, FN = TN / MF;     // MFMA blocks per wave
   static constexpr int KK = BK / (MF == 32 ? 16 : 32); // MFMA k-steps per k-tile
@@ -303,15 +303,15 @@ struct Geo {
 // 160 channels (widths divisible by 160 and not by 128, such as 320):
 // 36 KB stages, four, one workgroup of eight waves of 32 pixels x 80
 // channels on 16x16x32 MFMAs, so a 320-wide map is two tiles across
-using Narrow = Geo<128, 64, 4, 1, 3, 32>;
-using Wide = Geo<128, 128, 4, 2, 4, 32>;
-using Mid = Geo<128, 160, 4, 2, 4, 16>;
+using Narrow = Geo<64, 4, 1, 3, 32>;
+using Wide = Geo<128, 4, 2, 4, 32>;
+using Mid = Geo<160, 4, 2, 4, 16>;
 }
 
 template <class G>
 __global__ __launch_bounds__(64 * G::NW) void conv3x3_mfma_kernel(UNetConvParams p, int splits) {
   using namespace conv;
-  constexpr int BM = G::BM, NW = G::NW, S = G::S, STAGE = G::STAGE, LPT = G::LPT, KK = G::KK;
+  constexpr int NW = G::NW, S = G::S, STAGE = G::STAGE, LPT = G::LPT, KK = G::KK;
   constexpr int MF = G::MF, FM = G::FM, FN = G::FN, TM = G::TM, TN = G::TN, SROW = G::SROW, CPR = G::CPR;
   using Acc = std::conditional_t<MF == 32, f32x16, f32x4>;
   constexpr int AR = MF == 32 ? 16 : 4;                // accumulator registers
@@ -546,7 +546,7 @@ struct ConvPlan {
 
 template <class G>
 static ConvPlan conv_best_splits(int geo, double a, double b, int M, int C, int C_out, double* best_us) {
-  const int tiles = ceil_div(M, G::BM) * (C_out / G::BN);
+  const int tiles = ceil_div(M, conv::BM) * (C_out / G::BN);
   const int slots = 256 * G::WPC;
   const int kts = 9 * (C / conv::BK);
   const double mb = (double)M * C_out * sizeof(float) / 1e6;
@@ -588,7 +588,7 @@ static void launch_conv(const UNetConvParams& p, int M, int sp, hipStream_t s) {
     return true;
   }();
   (void)attr;
-  const int tiles = ceil_div(M, G::BM) * (p.C_out / G::BN);
+  const int tiles = ceil_div(M, conv::BM) * (p.C_out / G::BN);
   hipLaunchKernelGGL(kern, dim3(tiles * sp), dim3(64 * G::NW), G::S * G::STAGE, s, p, sp);
 }
 
