@@ -782,13 +782,18 @@ static AttnPlan plan_attention(int B, int heads, int n_q, int n_kv, int d) {
   constexpr int kCutTiles = 12;
   if (per % nkt == 0 || per + kCutTiles >= whole_longest) return {nkt, tiles, 0};
   // Up to kAlignTiles longer ranges that divide a query tile's key tiles: then no
-  // workgroup has a second segment, which costs more than they do (2 x 16 heads,
-  // 4096 keys: 384 queries, 12 -> 16 key tiles, 33.0 -> 29.9 us with the merge; 768
-  // queries, 24 -> 32, 42.9 -> 43.1; 640 queries, 20 -> 32, 39.2 -> 40.8).
+  // workgroup has a second segment, which costs more than they do (2 x 16 heads of
+  // 72, 4096 keys: 384 queries, 12 -> 16 key tiles, 30.5 -> 27.1 us with the merge; 768
+  // queries, 24 -> 32, 42.4 -> 42.4; 640 queries, 20 -> 32, 38.7 -> 40.2).  At 64
+  // channels ranges over twelve grow by 4, or by up to a quarter (10 heads, 144 queries x
+  // 5184 keys, 4 -> 9 19.3 -> 16.5 us; 16 heads, 640 x 4096, 10 -> 16 26.7 -> 26.2; 10 heads,
+  // 880 x 6400, 14 -> 20 29.5 -> 30.8; 4 heads, 1680 x 12544, 22 -> 28 37.5 -> 38.5; 12 heads,
+  // 560 x 12544, 23 -> 28 39.6 -> 38.3).
   constexpr int kAlignTiles = 6;
-  for (int d = per; d <= per + kAlignTiles && d < nkt; ++d)
-    if (nkt % d == 0) {
-      per = d;
+  const int longer = d == 64 && per > 12 ? cmin(kAlignTiles, cmax(4, per / 4)) : kAlignTiles;
+  for (int r = per; r <= per + longer && r < nkt; ++r)
+    if (nkt % r == 0) {
+      per = r;
       break;
     }
   const int workers = (int)((units + per - 1) / per);

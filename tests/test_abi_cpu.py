@@ -189,6 +189,19 @@ def test_library_speeds_reject(orch_lib, profs, ref, word):
     assert e.value.code == orch_lib.ORCH_EINVAL and word in orch_lib.last_error()
 
 
+@pytest.mark.parametrize("heads,n_q,n_kv,d,workers", [
+    # key tiles in all over the range each workgroup takes: the range lengthened to a divisor of
+    # a query tile's key tiles
+    (10, 880, 6400, 64, 500),     # 64 channels, 14 of 100: 20 is more than 4 and a quarter longer
+    (10, 144, 5184, 64, 180),     # 4 -> 9 of 81 (ranges up to twelve)
+    (12, 560, 12544, 64, 420),    # 23 -> 28 of 196 (up to a quarter)
+    (10, 880, 6400, 72, 350),     # 72 channels: 14 -> 20
+])
+def test_attention_plan_ranges(orch_lib, heads, n_q, n_kv, d, workers):
+    parts = 2 * workers * 128
+    assert orch_lib.attention_workspace_bytes(1, heads, n_q, n_kv, d, 1) == _al256(parts * d * 2) + parts * 8
+
+
 def _al256(b):
     return (b + 255) // 256 * 256
 

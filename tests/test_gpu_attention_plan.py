@@ -16,6 +16,7 @@ pytestmark = pytest.mark.gpu
     (1, 16, 72, 384, 4096, 0, 384),       # 6 -> 8
     (2, 16, 72, 640, 4096, 64, 640),      # 20, not 32: ranges cross tiles
     (1, 6, 64, 1024, 4096, 0, 1024),      # 64 channels
+    (1, 10, 64, 880, 6400, 0, 880),       # 14, not 20 of 100
     (2, 16, 72, 96, 64 * 61, 8, 96),      # 61 key tiles: no divisor near
 ])
 def test_attention_plan(orch_lib, B, heads, d, n_q, n_kv, fb, nf):
