@@ -117,14 +117,14 @@ def check(rc: int) -> None:
 
 
 def _ptr(t):
-    """Device address of a torch tensor (or None)."""
-    return None if t is None else C.c_void_p(t.data_ptr())
+    """Device address of a torch tensor (or None), as the pointer arguments take it."""
+    return None if t is None else t.data_ptr()
 
 
 def _stream(stream=None):
     import torch
     s = torch.cuda.current_stream() if stream is None else stream
-    return C.c_void_p(s.cuda_stream)
+    return s.cuda_stream
 
 
 def schedule_coefficients(cfg, t: int, t_prev: int, eta: float = 0.0):
@@ -245,7 +245,7 @@ def layernorm_modulate(x, rows, hidden, rows_per_batch, shift, scale, mod_stride
 
 def linear(A, M, K, W, N, bias, epilogue, gate, gate_stride, rows_per_batch, out, dtype,
            stream=None, workspace=None):
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    ws_bytes = 0 if workspace is None else workspace.nbytes
     check(lib.orch_op_linear(_ptr(A), M, K, _ptr(W), N, _ptr(bias), epilogue, _ptr(gate),
                              gate_stride, rows_per_batch, _ptr(out), _ptr(workspace), ws_bytes,
                              dtype, _stream(stream)))
@@ -268,7 +268,7 @@ def attention_workspace_bytes(B, heads, n_q, n_kv, head_dim, dtype) -> int:
 
 def attention(q, kv_stale, stale_bs, kv_fresh, fresh_bs, fresh_begin, n_fresh, B, heads, n_q,
               n_kv, head_dim, out, dtype, workspace=None, stream=None):
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    ws_bytes = 0 if workspace is None else workspace.nbytes
     check(lib.orch_op_attention(_ptr(q), _ptr(kv_stale), stale_bs, _ptr(kv_fresh), fresh_bs,
                                 fresh_begin, n_fresh, B, heads, n_q, n_kv, head_dim, _ptr(out),
                                 _ptr(workspace), ws_bytes, dtype, _stream(stream)))
