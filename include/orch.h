@@ -302,9 +302,10 @@ enum { ORCH_EPI_STORE = 0, ORCH_EPI_GELU = 1, ORCH_EPI_RESIDUAL = 2 };
  * workspace: device memory of at least orch_linear_workspace_bytes() bytes
  * (16-byte aligned) lets a GEMM with too few output tiles to fill the GPU
  * split K over more workgroups (fp32 partials, then a reduction that applies
- * the epilogue) or over the waves of a workgroup; NULL runs unsplit: an
- * output's summation order is then fixed by K alone, not by M.  The result
- * does not depend on the split beyond rounding. */
+ * the epilogue) or over the waves of a workgroup; fewer bytes allow fewer
+ * splits over workgroups and none over waves; NULL runs unsplit: an output's
+ * summation order is then fixed by K alone, not by M.  The result does not
+ * depend on the split beyond rounding. */
 int orch_op_linear(const void* A, int M, int K, const void* W, int N, const float* bias,
                    int epilogue, const float* gate, int gate_stride, int rows_per_batch,
                    void* out, void* workspace, size_t workspace_bytes, int dtype,

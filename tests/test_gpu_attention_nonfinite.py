@@ -63,8 +63,8 @@ def test_infinite_value_in_short_group(orch_lib, dtype, d, n_kv, key):
 @pytest.mark.parametrize("dtype,d,split", [("bf16", 64, True), ("bf16", 80, True), ("bf16", 128, True), ("f32", 32, True),
                                            ("f32", 72, True), ("bf16", 80, False), ("bf16", 128, False)])
 # key ranges (32 keys a tile); the whole range only where a finite score is left
-@pytest.mark.parametrize("masked,value", [((a, b), v) for a, b in ((32, 64), (1, 224), (224, 256))
-                                          for v in (-INF, -3.0e38, -1.7e38, -2.9e25)] + [((0, 256), -3.0e38)])
+@pytest.mark.parametrize("masked,value", [((32, 64), -INF), ((1, 224), -INF), ((32, 64), -2.9e25), ((1, 224), -3.0e38),
+                                          ((224, 256), -1.7e38), ((0, 256), -3.0e38)])
 def test_masked_keys(orch_lib, dtype, d, split, masked, value):
     """Keys masked through a channel of their own (1 in Q): scores of -infinity, or
     the lowest ones (every key masked: all alike)."""
